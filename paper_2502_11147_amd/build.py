@@ -3,26 +3,32 @@ from __future__ import annotations
 
 import hashlib
 import os
+import shutil
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB_PATH = os.path.join(HERE, "libraas.so")
-SOURCES = [os.path.join(CSRC, "raas_kernels.hip"), os.path.join(CSRC, "raas_runtime.hip")]
+KERNELS = os.path.join(CSRC, "raas_kernels.hip")
+# translation units of libraas.so: the kernels' file once per RAAS_PART, and the runtime
+KERNEL_PARTS = 7
+UNITS = [(KERNELS, ["-DRAAS_PART=%d" % i]) for i in range(KERNEL_PARTS)] + [(os.path.join(CSRC, "raas_runtime.hip"), [])]
 # the streaming probe (measurement only) is a library of its own
 PROBE_SOURCES = [os.path.join(CSRC, "raas_probe.hip")]
 PROBE_LIB_PATH = os.path.join(HERE, "libraas_probe.so")
 ARCH = "gfx950"
 
 
-def hipcc_command(out: str, sources=None) -> list[str]:
+def hipcc_command(out: str, sources, *more: str) -> list[str]:
     return [
-        "hipcc", "--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-shared",
+        "hipcc", "--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", *more,
         # packed fp32 vector instructions stay off on this target
         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-        "-I", INCLUDE, "-I", CSRC, *(SOURCES if sources is None else sources), "-o", out,
+        "-I", INCLUDE, "-I", CSRC, *sources, "-o", out,
     ]
 
 
@@ -49,29 +55,36 @@ def kernel_digest() -> str:
     and the compile flags: identifies the kernels that a stored
     hardware-counter measurement was taken on."""
     h = hashlib.sha256()
-    for p in (os.path.join(CSRC, "raas_kernels.hip"), os.path.join(CSRC, "raas_internal.h")):
+    for p in (KERNELS, os.path.join(CSRC, "raas_internal.h")):
         with open(p, encoding="utf-8") as f:
             h.update(_code_text(f.read()).encode())
-    h.update(" ".join(a for a in hipcc_command("lib") if not os.path.isabs(a) and a not in ("-I", "-o", "lib")).encode())
+    h.update(" ".join(a for a in hipcc_command("lib", (), "-shared") if not os.path.isabs(a) and a not in ("-I", "-o", "lib")).encode())
     return h.hexdigest()
 
 
-def _compile(out: str, sources, verbose: bool):
-    tmp = out + ".tmp%d" % os.getpid()
-    cmd = hipcc_command(tmp, sources)
+def _hipcc(cmd: list[str], verbose: bool):
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
     if verbose:
         print(" ".join(cmd))
-    os.replace(tmp, out)
 
 
 def build(verbose: bool = False) -> str:
     """Builds libraas.so (the decode path) and libraas_probe.so (the
     streaming probe of the measurements)."""
-    _compile(LIB_PATH, SOURCES, verbose)
-    _compile(PROBE_LIB_PATH, PROBE_SOURCES, verbose)
+    with tempfile.TemporaryDirectory(prefix="raas_build_") as tmp:
+        objects = [os.path.join(tmp, "unit%d.o" % i) for i in range(len(UNITS))]
+        lib, probe = os.path.join(tmp, "libraas.so"), os.path.join(tmp, "libraas_probe.so")
+        compiles = [hipcc_command(o, [src], "-c", *flags) for o, (src, flags) in zip(objects, UNITS)]
+        compiles.append(hipcc_command(probe, PROBE_SOURCES, "-shared"))
+        with ThreadPoolExecutor(max(1, min(8, os.cpu_count() or 1))) as pool:
+            list(pool.map(lambda c: _hipcc(c, verbose), compiles))
+        _hipcc(hipcc_command(lib, objects, "-shared"), verbose)
+        for src, dst in ((lib, LIB_PATH), (probe, PROBE_LIB_PATH)):
+            part = dst + ".tmp%d" % os.getpid()
+            shutil.copyfile(src, part)
+            os.replace(part, dst)
     return LIB_PATH
 
 

@@ -41,6 +41,7 @@ struct LayerView {
     int32_t* err;    // device flag, nonzero after an internal inconsistency
     double* score;   // split path: [U][S] page scores; [U][S][G] per-head bounds when agg == 1
     float* part;     // [U][nsplit][G][D+2] partial attention (split path)
+    int32_t* arrived;  // [U] splits of the unit, [U / hgrp] units of the decision that have published; zero between launches
     int U, G, D, ps, S, Lcap;
     int nsplit, bps;  // attention splits per unit, 32-token blocks per split
     int rev;          // 1: this step visits blocks and page groups in descending order
@@ -97,10 +98,10 @@ struct StepPlan {
 // unchosen prompt blocks); grouped: retention decided per group of units, by
 // the epilogue kernel;
 // list_ints: LDS ints of a block list or of the in-step prompt selection (0
-// without a prompt region)
+// without a prompt region); fixed_scratch: raas_decode_step_static
 StepPlan plan_step(int U, int G, int D, int S, int Lcap, int ps, int work_blocks, bool bf16, int agg,
                    bool grouped, int list_ints, int split_override,
-                   int npr);
+                   int npr, int nkv, bool fixed_scratch);
 // Quest on the prompt pages: the attended fills and the block list of a step.
 hipError_t launch_prompt_select(const LayerView& L, const StepIO& io, hipStream_t stream);
 // Lets the step kernels use more than the default dynamic LDS.
@@ -110,11 +111,11 @@ hipError_t allow_large_lds();
 // max_tok: the most tokens any selected unit keeps (min(P, kept pages * ps)).
 hipError_t launch_prefill(const LayerView& L, const void* k, const void* v, const PrefillIn& in, int max_tok,
                           hipStream_t stream);
-// The step kernel: attention, page scores, append; plus the epilogue when fused.
+// The step kernel: the whole step (bf16 and fused fp32 plans), or attention, page scores and append.
 hipError_t launch_step(const LayerView& L, const StepIO& io, const StepPlan& plan, double r,
                        hipStream_t stream);
-// The epilogue kernel of the split path: merge, refresh, evict, state out;
-// one workgroup per group of L.hgrp units.
+// The epilogue kernel of the fp32 split path: merge, refresh, evict, state
+// out; one workgroup per group of L.hgrp units.
 hipError_t launch_epilogue(const LayerView& L, const StepIO& io, double r, hipStream_t stream);
 
 }  // namespace raas

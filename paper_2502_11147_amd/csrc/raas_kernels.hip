@@ -23,6 +23,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <utility>
 
 #include "raas_internal.h"
@@ -256,12 +257,46 @@ __device__ __forceinline__ void stage_slot(const UnitRec& ur, int s, int st, int
     s_score[s] = INFINITY;  // scored below when evictable; never ranks under a real score
 }
 
-__device__ void load_slots(const LayerView& L, int u, const UnitRec& ur, double* s_score, int* s_state,
+__device__ __forceinline__ void load_slots(const LayerView& L, int u, const UnitRec& ur, double* s_score, int* s_state,
                            int* s_ts, int* s_lid, int first = 0) {
     const int S = L.S;
     const size_t base = (size_t)u * S;
     for (int s = threadIdx.x + first; s < S; s += blockDim.x)
         stage_slot(ur, s, L.state[base + s], L.ts[base + s], L.lid[base + s], s_score, s_state, s_ts, s_lid);
+}
+
+// ---------------------------------------------------------------------------
+// Results handed from one workgroup to another inside a launch. The L2s of
+// the XCDs are not coherent with each other, and an agent-scope release
+// writes back a whole L2 (6 to 9 us per step with hundreds of workgroups
+// doing so). So the few kilobytes that cross workgroups are written with
+// agent-scope (write-through) stores and read with agent-scope loads, which
+// miss the L2: once a wavefront's stores have been acknowledged (vmcnt 0)
+// they are where every XCD reads them, and nothing needs to be written back.
+template <typename T>
+__device__ __forceinline__ void publish(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T published(const T* p) {
+    return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// True on the last of `total` workgroups to call it for this counter, once
+// everything that all of them published before is readable. The counter goes
+// back to zero for the next launch. No workgroup waits for another. Every
+// thread of the workgroup calls it; s_last: one LDS int.
+__device__ __forceinline__ bool arrive_last(int32_t* counter, int total, int* s_last) {
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0);  // this wavefront's stores are acknowledged
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int before = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (before == total - 1) publish(counter, 0);
+        *s_last = before == total - 1;
+    }
+    __syncthreads();
+    return *s_last != 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -423,7 +458,7 @@ __device__ __forceinline__ double score_finish(const LayerView& L, int u, int p,
         a += dpp_f64<0x4E>(a);
         a += dpp_f64<0x141>(a);
         best = a > best ? a : best;
-        if (hb != nullptr && part == 0) hb[j] = a;  // per-head bounds, for the softmax aggregation
+        if (hb != nullptr && part == 0) publish(hb + j, a);  // per-head bounds, for the softmax aggregation
     }
     return best;
 }
@@ -609,22 +644,34 @@ struct RetShared {
 // deciding together; hb[((h*S) + p)*G + j] holds head j of unit h's bound of
 // page p for every ranked page p. First one wavefront per head finds M and Z
 // (into s_mz), then one thread per page sums its terms; s_score is visible
-// to the whole workgroup on return.
-__device__ void softmax_sum_block(const LayerView& L, const double* hb, int nu, const int* s_state,
-                                  double* s_score, double* s_mz, int tid, int nthreads) {
+// to the whole workgroup on return. The fp64 exponentials are the cost: with
+// the bounds in LDS (PUB false) each replaces its bound, so that it is taken
+// once; bounds too many for that are read as published (PUB) and take it
+// twice.
+template <bool PUB>
+__device__ __forceinline__ void softmax_sum_block(const LayerView& L, double* hb, int nu, const int* s_state,
+                                                  double* s_score, double* s_mz, int tid, int nthreads) {
+    auto bound = [](const double* p) {
+        if constexpr (PUB) return published(p);
+        else return *p;
+    };
     const int S = L.S, G = L.G, H = nu * G, lane = tid & 63, nw = nthreads >> 6;
     const double c = 1.0 / sqrt((double)L.D);
     for (int hj = tid >> 6; hj < H; hj += nw) {
         const int h = hj / G, j = hj - (hj / G) * G;
-        const double* hbj = hb + (size_t)h * S * G + j;
+        double* hbj = hb + (size_t)h * S * G + j;
         double mx = -INFINITY;
         for (int p = lane; p < S; p += 64)
-            if (ranked(L, s_state[p])) mx = fmax(mx, hbj[(size_t)p * G]);
+            if (ranked(L, s_state[p])) mx = fmax(mx, bound(hbj + (size_t)p * G));
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
         double z = 0.0;
         for (int p = lane; p < S; p += 64)
-            if (ranked(L, s_state[p])) z += exp(c * (hbj[(size_t)p * G] - mx));
+            if (ranked(L, s_state[p])) {
+                const double e = exp(c * (bound(hbj + (size_t)p * G) - mx));
+                if (!PUB) hbj[(size_t)p * G] = e;
+                z += e;
+            }
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) z += __shfl_xor(z, off);
         if (lane == 0) {
@@ -636,14 +683,23 @@ __device__ void softmax_sum_block(const LayerView& L, const double* hb, int nu, 
     for (int p = tid; p < S; p += nthreads) {
         if (!ranked(L, s_state[p])) continue;
         double acc = 0.0;
-#pragma unroll 8
+#pragma unroll 4
         for (int hj = 0; hj < H; ++hj) {
             const int h = hj / G, j = hj - (hj / G) * G;
-            acc += exp(c * (hb[((size_t)h * S + p) * G + j] - s_mz[2 * hj])) / s_mz[2 * hj + 1];
+            const double b = bound(hb + ((size_t)h * S + p) * G + j);
+            acc += (PUB ? exp(c * (b - s_mz[2 * hj])) : b) / s_mz[2 * hj + 1];
         }
         s_score[p] = acc;
     }
     __syncthreads();
+}
+
+// Makes this wavefront's LDS writes visible to its own later LDS reads (the
+// lanes of one wavefront exchanging data through LDS; no workgroup barrier).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Retention policy of one unit, run by one wavefront (Algorithm 1, the
@@ -660,13 +716,13 @@ __device__ void softmax_sum_block(const LayerView& L, const double* hb, int nu, 
 //    the smallest (timestamp, logical id) is freed;
 //  - the next token's target: the tail page if it has room, else the lowest
 //    free slot (a fresh page).
-__device__ void evict_wave(const LayerView& L, const UnitRec& ur, int* s_state, int* s_ts, const int* s_lid,
+__device__ __forceinline__ void evict_wave(const LayerView& L, const UnitRec& ur, int* s_state, int* s_ts, const int* s_lid,
                            RetShared& out);
 
 // lo: where the rank count starts, at most the first slot that a ranked
 // page can occupy (slots below the decode base, and below the unit's pinned
 // pages unless the pool ranks them, hold none).
-__device__ void retention_wave(const LayerView& L, const UnitRec& ur, double r, const double* s_score,
+__device__ __forceinline__ void retention_wave(const LayerView& L, const UnitRec& ur, double r, const double* s_score,
                                int* s_state, int* s_ts, const int* s_lid, RetShared& out, int lo) {
     const int S = L.S, lane = threadIdx.x & 63, s_lo = lo;
     int n = 0;
@@ -677,13 +733,20 @@ __device__ void retention_wave(const LayerView& L, const UnitRec& ur, double r, 
     }
     const int k = (int)floor(r * (double)n);
     if (k > 0) {
+        // two scores per LDS read (s_score is 16-byte aligned; slots below lo
+        // hold +inf), and the last of an odd S
+        const double2* sc2 = reinterpret_cast<const double2*>(s_score);
+        const double last = (S & 1) ? s_score[S - 1] : INFINITY;
         for (int s0 = s_lo; s0 < S; s0 += 64) {
             const int p = s0 + lane;
             if (p < S && s_state[p] == kEvictable) {
                 const double sp = s_score[p];
-                int less = 0;
+                int less = last < sp ? 1 : 0;
 #pragma unroll 8
-                for (int o = s_lo; o < S; ++o) less += s_score[o] < sp;
+                for (int o = s_lo >> 1; o < S >> 1; ++o) {
+                    const double2 x = sc2[o];
+                    less += (x.x < sp ? 1 : 0) + (x.y < sp ? 1 : 0);
+                }
                 if (less >= n - k) s_ts[p] = ur.clock;
             }
         }
@@ -693,7 +756,7 @@ __device__ void retention_wave(const LayerView& L, const UnitRec& ur, double r, 
 
 // Eviction and the next token's target, by one wavefront, once the refresh
 // has set the timestamps.
-__device__ void evict_wave(const LayerView& L, const UnitRec& ur, int* s_state, int* s_ts, const int* s_lid,
+__device__ __forceinline__ void evict_wave(const LayerView& L, const UnitRec& ur, int* s_state, int* s_ts, const int* s_lid,
                            RetShared& out) {
     const int S = L.S, ps = L.ps, lane = threadIdx.x & 63;
     int nfree = 0;  // free decode slots
@@ -791,8 +854,138 @@ __device__ double kth_largest_f64_wg(const double* x, int n, int k, int* hist, i
     return from_order_key(prefix);
 }
 
-// Top-r refresh by a whole workgroup (every thread calls it; the epilogue
-// kernel's version of the rule in retention_wave). With n ranked pages and
+// The number of ranked slots among those this thread staged, added up over the
+// workgroup into *s_n (zero before, complete after the caller's next barrier).
+__device__ __forceinline__ void count_ranked(bool mine, int* s_n) {
+    const unsigned long long m = __ballot(mine);
+    if ((threadIdx.x & 63) == 0 && m) atomicAdd(s_n, __popcll(m));
+}
+
+// Top-r refresh and eviction by a whole workgroup (every thread calls it; the
+// version of the rules in retention_wave for split units and for the fp32
+// epilogue kernel): with n ranked pages and k = floor(r*n), an evictable page is
+// refreshed when at least n-k ranked pages score strictly less. meanwhile():
+// the caller's own work, done by the other wavefronts while wavefront 0
+// evicts. Slots below first hold no ranked page (the prompt region's, and
+// pinned pages that are not ranked), so no loop starts before it: a long
+// pinned prompt costs nothing here.
+// Up to 64 slots wavefront 0 counts the lower scores (two per LDS read); up to
+// 256 every thread, a slot's count spread over as many as there are (into
+// s_less, zero before). Beyond, the workgroup finds theta, the (n-k)-th
+// smallest ranked score, by a radix select over order_key (8-bit digits, most
+// significant first, a 256-bin histogram each) and refreshes the evictable
+// pages scoring above theta: the same pages, since fewer than n-k ranked scores
+// lie below theta and at least n-k lie at or below it. It stops at the digit
+// that leaves theta alone in its bin (the third, mostly), when a larger prefix
+// means a larger score. s_score: 16-byte aligned, [S] and one more slot when S
+// is odd; s_less: [S] ints; s_aux: 261 ints. The caller's barrier comes before
+// and after.
+template <class F>
+__device__ __forceinline__ void retention_block(const LayerView& L, const UnitRec& ur, double r, int n,
+                                                const double* s_score, int* s_state, int* s_ts, const int* s_lid,
+                                                int* s_less, int* s_aux, RetShared& out, int tid, int nthreads,
+                                                int first, F&& meanwhile) {
+    const int S = L.S, lane = tid & 63, nsl = S - first;
+    const int k = (int)floor(r * (double)n);
+    const double2* sc2 = reinterpret_cast<const double2*>(s_score);
+    const int pair0 = first >> 1, pair1 = (S + 1) >> 1;  // (slots below first and the one past S hold +inf)
+    if (k > 0 && k < n && nsl <= 64) {
+        if (tid < 64 && first + tid < S && s_state[first + tid] == kEvictable) {
+            const double sp = s_score[first + tid];
+            int less = 0;
+#pragma unroll 8
+            for (int o = pair0; o < pair1; ++o) {
+                const double2 x = sc2[o];
+                less += (x.x < sp ? 1 : 0) + (x.y < sp ? 1 : 0);
+            }
+            if (less >= n - k) s_ts[first + tid] = ur.clock;
+        }
+    } else if (k > 0 && k < n && nsl <= 256) {
+        // slot first + i % wide, the pairs of scores share, share + shares, ...
+        const int log_wide = nsl <= 128 ? 7 : 8, shares = max(1, nthreads >> log_wide);
+        for (int i = tid; i < shares << log_wide; i += nthreads) {
+            const int share = i >> log_wide, p = first + i - (share << log_wide);
+            if (p >= S || s_state[p] != kEvictable) continue;
+            const double sp = s_score[p];
+            int less = 0;
+#pragma unroll 8
+            for (int o = pair0 + share; o < pair1; o += shares) {
+                const double2 x = sc2[o];
+                less += (x.x < sp ? 1 : 0) + (x.y < sp ? 1 : 0);
+            }
+            if (less) atomicAdd(&s_less[p], less);
+        }
+        __syncthreads();
+        if (tid < 64) {
+            for (int p = first + tid; p < S; p += 64)
+                if (s_state[p] == kEvictable && s_less[p] >= n - k) s_ts[p] = ur.clock;
+        }
+    } else if (k > 0) {
+        unsigned long long prefix = 0, mask = 0;
+        int want = n - k - 1;  // 0-based rank of theta among the ranked scores that match prefix
+        for (int shift = 56; shift >= 0 && k < n; shift -= 8) {
+            for (int b = tid; b < 256; b += nthreads) s_aux[b] = 0;
+            __syncthreads();
+            for (int p = first + tid; p < S; p += nthreads) {
+                if (!ranked(L, s_state[p])) continue;
+                const unsigned long long key = order_key(s_score[p] + 0.0);  // (-0 counts as +0)
+                if ((key & mask) == prefix) atomicAdd(&s_aux[(int)((key >> shift) & 255ull)], 1);
+            }
+            __syncthreads();
+            if (tid < 64) {  // wavefront 0 scans the bins: lane l holds bins 4l .. 4l+3
+                const int c0 = s_aux[4 * lane], c1 = s_aux[4 * lane + 1], c2 = s_aux[4 * lane + 2],
+                          c3 = s_aux[4 * lane + 3];
+                const int sum = c0 + c1 + c2 + c3;
+                int incl = sum;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const int v = __shfl_up(incl, off);
+                    if (lane >= off) incl += v;
+                }
+                const int excl = incl - sum;
+                if (excl <= want && want < incl) {
+                    int w = want - excl, b = 4 * lane, c = c0;
+                    if (w >= c0) {
+                        w -= c0;
+                        ++b;
+                        c = c1;
+                        if (w >= c1) {
+                            w -= c1;
+                            ++b;
+                            c = c2;
+                            if (w >= c2) {
+                                w -= c2;
+                                ++b;
+                                c = c3;
+                            }
+                        }
+                    }
+                    s_aux[257] = b;
+                    s_aux[258] = w;
+                    s_aux[259] = c;
+                }
+            }
+            __syncthreads();
+            prefix |= (unsigned long long)s_aux[257] << shift;
+            mask |= 255ull << shift;
+            want = s_aux[258];
+            if (s_aux[259] == 1) break;
+        }
+        // (k == n: no digit was taken, and every page is refreshed)
+        for (int p = first + tid; p < S; p += nthreads)
+            if (s_state[p] == kEvictable && (k == n || (order_key(s_score[p] + 0.0) & mask) > prefix))
+                s_ts[p] = ur.clock;
+        __syncthreads();
+    }
+    if (tid < 64) {
+        wave_lds_sync();
+        evict_wave(L, ur, s_state, s_ts, s_lid, out);
+    }
+    meanwhile();
+}
+
+// Top-r refresh by a whole workgroup (every thread calls it; the fused
+// fp32 kernel's version of the rule in retention_wave). With n ranked pages and
 // k = floor(r*n), an evictable page is refreshed when at least n-k ranked
 // pages score strictly less. Up to 256 slots this is counted directly.
 // Beyond, the workgroup finds theta, the (n-k)-th smallest ranked score, by
@@ -884,7 +1077,7 @@ __device__ void refresh_block(const LayerView& L, const UnitRec& ur, double r, c
 }
 
 // Writes the step's retention results to the pool and the optional outputs.
-__device__ void retention_store(const LayerView& L, const StepIO& io, int u, const UnitRec& ur,
+__device__ __forceinline__ void retention_store(const LayerView& L, const StepIO& io, int u, const UnitRec& ur,
                                 const int* s_state, const int* s_ts, const int* s_lid, const RetShared& rs,
                                 int first, int stride) {
     const int S = L.S;
@@ -913,14 +1106,6 @@ __device__ void retention_store(const LayerView& L, const StepIO& io, int u, con
         if (io.evicted_out) io.evicted_out[u] = rs.evicted;
         if (rs.errs) atomicOr(L.err, rs.errs);
     }
-}
-
-// Makes this wavefront's LDS writes visible to its own later LDS reads (the
-// lanes of one wavefront exchanging data through LDS; no workgroup barrier).
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Waits for every vector-memory load in flight (vmcnt(0); expcnt and lgkmcnt left at their maxima).
@@ -961,6 +1146,148 @@ __device__ float kth_largest_wg(const float* x, int n, int k, int* hist, int tid
         want = hist[257];
     }
     return from_ukey_f32(prefix);
+}
+
+// Merge of unit u's splits (out = sum_s 2^(M_s - M) O_s / sum_s 2^(M_s - M)
+// L_s) from their published partials, by a whole workgroup, in two parts, so
+// that every read of the first part is in flight together with the caller's
+// own: kMergeAhead splits of this thread's first output, and item tid of the
+// splits' maxima and sums. s_ml: [nsplit][G][2] floats of LDS.
+constexpr int kMergeAhead = 16;
+struct MergeFirst {
+    float m, l, o[kMergeAhead];
+};
+__device__ __forceinline__ MergeFirst merge_first(const LayerView& L, int u, int tid) {
+    const int G = L.G, D = L.D, nsplit = L.nsplit;
+    const float* pu = L.part + (size_t)u * nsplit * G * (D + 2);
+    MergeFirst f;
+    const float* pm = pu + (size_t)min(tid, nsplit * G - 1) * (D + 2) + D;
+    f.m = published(pm);
+    f.l = published(pm + 1);
+    const int idx = min(tid, G * D - 1), h = idx / D, c = idx - (idx / D) * D;
+#pragma unroll
+    for (int s = 0; s < kMergeAhead; ++s) f.o[s] = published(pu + ((size_t)min(s, nsplit - 1) * G + h) * (D + 2) + c);
+    return f;
+}
+// every split's running max and sum into s_ml (visible after the caller's barrier)
+__device__ __forceinline__ void merge_stage(const LayerView& L, int u, const MergeFirst& f, float* s_ml, int tid,
+                                            int nth) {
+    const int G = L.G, D = L.D, nsplit = L.nsplit;
+    const float* pu = L.part + (size_t)u * nsplit * G * (D + 2);
+    if (tid < nsplit * G) {
+        s_ml[2 * tid] = f.m;
+        s_ml[2 * tid + 1] = f.l;
+    }
+    for (int i = tid + nth; i < nsplit * G; i += nth) {
+        s_ml[2 * i] = published(pu + (size_t)i * (D + 2) + D);
+        s_ml[2 * i + 1] = published(pu + (size_t)i * (D + 2) + D + 1);
+    }
+}
+template <typename T>
+__device__ __forceinline__ void merge_out(const LayerView& L, const StepIO& io, int u, const MergeFirst& f,
+                                          const float* s_ml, int tid, int nth) {
+    const int G = L.G, D = L.D, nsplit = L.nsplit;
+    const float* pu = L.part + (size_t)u * nsplit * G * (D + 2);
+    for (int idx = tid; idx < G * D; idx += nth) {
+        const int h = idx / D, c = idx - (idx / D) * D;
+        float M = -INFINITY;
+        for (int s = 0; s < nsplit; ++s) M = fmaxf(M, s_ml[2 * (s * G + h)]);
+        float O = 0.0f, Ls = 0.0f;
+        for (int s0 = 0; s0 < nsplit; s0 += kMergeAhead) {
+            float o[kMergeAhead];
+            if (idx == tid && s0 == 0) {
+#pragma unroll
+                for (int e = 0; e < kMergeAhead; ++e) o[e] = f.o[e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < kMergeAhead; ++e)
+                    o[e] = published(pu + ((size_t)min(s0 + e, nsplit - 1) * G + h) * (D + 2) + c);
+            }
+#pragma unroll
+            for (int e = 0; e < kMergeAhead; ++e) {
+                if (s0 + e >= nsplit) break;
+                const float ms = s_ml[2 * ((s0 + e) * G + h)];
+                const float wt = (ms == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(ms - M);
+                O += wt * o[e];
+                Ls += wt * s_ml[2 * ((s0 + e) * G + h) + 1];
+            }
+        }
+        ((T*)io.out)[((size_t)u * G + h) * D + c] = from_f<T>(O / Ls);
+    }
+}
+
+// LDS bytes of finish_units: scores, slot records and counts, the softmax
+// aggregation's M and Z and (where they fit kMaxStagedBounds) its bounds, the
+// splits' maxima and sums
+constexpr size_t kMaxStagedBounds = 64 * 1024;
+__host__ __device__ constexpr size_t staged_bounds(int G, int S, int agg, int nu) {
+    const size_t b = agg ? (size_t)nu * S * G * 8 : 0;
+    return b <= kMaxStagedBounds ? b : 0;
+}
+__host__ __device__ constexpr size_t finish_lds(int G, int S, int nsplit, int agg, int nu) {
+    return (size_t)(S + (S & 1)) * 8 + staged_bounds(G, S, agg, nu) + (agg ? (size_t)nu * G * 16 : 0) +
+           (size_t)S * 16 + (size_t)2 * nsplit * G * 4;
+}
+
+// What is left of a step once the splits of every unit of a decision have
+// published their page scores (and, with merge, their partial attention): the
+// retention policy, the merge, and the state out, by one workgroup (every
+// thread calls it). A decision covers units u0 .. u0+nu-1: one unit, or the KV
+// heads of a sequence when they share one page table (whose slot states are
+// then identical), a page's score aggregating the bounds of all their heads;
+// merge (of unit u0) goes with nu 1. This is one chain of latencies, so its
+// reads (scores, slot records, partials) all go out together, and wavefront 0
+// evicts while the others merge. smem: finish_lds bytes of LDS, 16-byte
+// aligned; s_aux: 261 ints.
+template <typename T>
+__device__ __forceinline__ void finish_units(const LayerView& L, const StepIO& io, double r, int u0, int nu,
+                                             bool merge, unsigned char* smem, int* s_aux, RetShared& ret, int tid,
+                                             int nth) {
+    const int S = L.S, G = L.G;
+    const size_t nhb = staged_bounds(G, S, L.agg, nu) / 8;
+    double* s_score = reinterpret_cast<double*>(smem);
+    double* s_hb = s_score + S + (S & 1);  // [nu][S][G], softmax aggregation only
+    double* s_mz = s_hb + nhb;             // [nu*G][2], likewise
+    int* s_state = reinterpret_cast<int*>(s_mz + (L.agg ? 2 * (size_t)nu * G : 0));
+    int* s_ts = s_state + S;
+    int* s_lid = s_ts + S;
+    int* s_less = s_lid + S;
+    float* s_ml = reinterpret_cast<float*>(s_less + S);
+    const size_t base = (size_t)u0 * S;
+    MergeFirst mf;
+    if (merge) mf = merge_first(L, u0, tid);
+    const UnitRec ur = read_unit(L, u0);
+    const int first = L.rank_pinned ? L.dbase : max(L.dbase, L.unit[(size_t)u0 * kUnitFields + kPinnedPages]);
+    if (tid == 0) {
+        s_aux[256] = 0;
+        if (S & 1) s_score[S] = INFINITY;
+    }
+    lds_barrier();  // (the count's zero; the reads stay in flight)
+    for (int s = tid; s < S; s += nth) {
+        double sc = INFINITY;
+        if (!L.agg) {  // max over the units; read whether or not the page turns out to be ranked
+            sc = published(L.score + base + s);
+#pragma unroll 8
+            for (int h = 1; h < nu; ++h) sc = fmax(sc, published(L.score + base + (size_t)h * S + s));
+        }
+        stage_slot(ur, s, L.state[base + s], L.ts[base + s], L.lid[base + s], s_score, s_state, s_ts, s_lid);
+        s_less[s] = 0;
+        const bool rk = ranked(L, s_state[s]);
+        if (rk && !L.agg) s_score[s] = sc;
+        count_ranked(rk, &s_aux[256]);
+    }
+    for (size_t i = tid; i < nhb; i += nth) s_hb[i] = published(L.score + base * G + i);
+    if (merge) merge_stage(L, u0, mf, s_ml, tid, nth);
+    __syncthreads();
+    if (L.agg) {
+        if (nhb > 0) softmax_sum_block<false>(L, s_hb, nu, s_state, s_score, s_mz, tid, nth);
+        else softmax_sum_block<true>(L, L.score + base * G, nu, s_state, s_score, s_mz, tid, nth);
+    }
+    retention_block(L, ur, r, s_aux[256], s_score, s_state, s_ts, s_lid, s_less, s_aux, ret, tid, nth, first, [&] {
+        if (merge) merge_out<T>(L, io, u0, mf, s_ml, tid, nth);
+    });
+    __syncthreads();
+    for (int uh = 0; uh < nu; ++uh) retention_store(L, io, u0 + uh, ur, s_state, s_ts, s_lid, ret, tid, nth);
 }
 
 // One 32-token block of attention for the GQA group held by this wavefront:
@@ -1045,12 +1372,15 @@ __device__ __forceinline__ void attend_block(const u32x4 (&kr)[2][D / 32], const
 // prompt blocks from one list. 0: no prompt region.
 // NT: K/V blocks are read with non-temporal loads (pools too large for the
 // memory-side cache to serve the next step).
+// SPLIT: the unit is spread over several workgroups, or decides with others,
+// and the last workgroup to end finishes the step (instances of their own:
+// in one kernel with the fused ones, that code cost the block loop spills).
 // The step of work item wi = unit * nsplit + split, by one workgroup (the
 // arguments by value: as kernel arguments, they leave the registers of the
 // block loop alone).
-template <int D, int NW, bool AGG, int LM, bool NT>
-__device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_log2, double r, int fused,
-                                          const int wi) {
+template <int D, int NW, bool AGG, int LM, bool NT, bool SPLIT>
+__device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_log2, double r, const int wi) {
+    constexpr bool fused = !SPLIT;
     constexpr int KS = D / 32, NB = D / 16, BLK = 32 * D;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ float s_m[NW][16];
@@ -1066,7 +1396,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
     const int G = L.G, S = L.S, ps = L.ps;
     float* s_qf = reinterpret_cast<float*>(smem);  // [G][D+32] q in fp32, padded: qpad_index
     float* s_o = s_qf + (size_t)G * qpad_row(D);   // [NW][G][D+4]
-    double* s_score = reinterpret_cast<double*>(s_o + (size_t)NW * G * (D + 4));  // [S], fused only
+    double* s_score = reinterpret_cast<double*>(s_o + (size_t)NW * G * (D + 4));  // [S], fused only, 16-byte aligned
     double* s_hb = s_score + S;  // [S][G] per-head bounds, fused softmax aggregation only
     double* s_mz = s_hb + (AGG ? (size_t)S * G : 0);  // [G][2] each head's M and Z, likewise
     int* s_state = reinterpret_cast<int*>(s_mz + (AGG ? 2 * G : 0));  // [S], fused only
@@ -1212,7 +1542,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
             st4(&s_kn[8 * tid], kn_first);
             st4(&s_vn[8 * tid], vn_first);
         }
-        if (fused) {  // (always, with LM 2)
+        {
             if (tid < S) stage_slot(ur, tid, st_first, ts_first, lid_first, s_score, s_state, s_ts, s_lid);
             if (tid + NW * 64 < S) stage_slot(ur, tid + NW * 64, st_sec, ts_sec, lid_sec, s_score, s_state, s_ts, s_lid);
             load_slots(L, u, ur, s_score, s_state, s_ts, s_lid, 2 * NW * 64);
@@ -1399,7 +1729,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
         const double sc = score_finish<D>(L, u, p, part, act_cur, frag, p == ns, opened, s_kn, s_qf, hb);
         if (act_cur && part == 0 && !AGG) {
             if (fused) s_score[p] = sc;
-            else L.score[base + p] = sc;
+            else publish(L.score + base + p, sc);
         }
         ++pass;
         if (pass < npass) {
@@ -1411,7 +1741,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
     // retention policy once every wavefront's scores are in LDS
     auto scores_done = [&]() {
         lds_barrier();
-        if (AGG && fused) softmax_sum_block(L, s_hb, 1, s_state, s_score, s_mz, tid, NW * 64);
+        if (AGG && fused) softmax_sum_block<false>(L, s_hb, 1, s_state, s_score, s_mz, tid, NW * 64);
         // (after the block loop, as with the softmax aggregation, the retention
         // is on the critical path: its count skips the pinned pages; mid-loop
         // it overlaps the streaming, and the narrower count measured no faster)
@@ -1538,20 +1868,36 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
             ((uint16_t*)io.out)[((size_t)u * G + h) * D + c] = f2bf(O / Ls);
         } else {
             float* pp = L.part + (((size_t)u * nsplit + split) * G + h) * (D + 2);
-            pp[c] = O;
+            publish(pp + c, O);
             if (c == 0) {
-                pp[D] = M;
-                pp[D + 1] = Ls;
+                publish(pp + D, M);
+                publish(pp + D + 1, Ls);
             }
         }
+    }
+    if constexpr (SPLIT) {
+        // The last workgroup of the unit to get here finishes its step; with
+        // one decision per sequence it merges the unit, and the last unit of
+        // the sequence decides.
+        __shared__ int s_last, s_aux[261];
+        const int nu = L.hgrp;
+        if (!arrive_last(L.arrived + u, nsplit, &s_last)) return;
+        if (nu > 1 && nsplit > 1) {
+            const MergeFirst mf = merge_first(L, u, tid);
+            merge_stage(L, u, mf, reinterpret_cast<float*>(smem), tid, NW * 64);
+            __syncthreads();
+            merge_out<uint16_t>(L, io, u, mf, reinterpret_cast<float*>(smem), tid, NW * 64);
+        }
+        if (nu > 1 && !arrive_last(L.arrived + L.U + u / nu, nu, &s_last)) return;
+        finish_units<uint16_t>(L, io, r, u / nu * nu, nu, nu == 1 && nsplit > 1, smem, s_aux, ret, tid, NW * 64);
     }
 }
 
 // Step kernel (bf16 pools): rows a1-a6 for work item blockIdx.x.
-template <int D, int NW, bool AGG, int LM, bool NT = false>
+template <int D, int NW, bool AGG, int LM, bool NT, bool SPLIT>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_bf16(
-    LayerView L, StepIO io, float scale_log2, double r, int fused) {
-    step_item<D, NW, AGG, LM, NT>(L, io, scale_log2, r, fused, blockIdx.x);
+    LayerView L, StepIO io, float scale_log2, double r) {
+    step_item<D, NW, AGG, LM, NT, SPLIT>(L, io, scale_log2, r, blockIdx.x);
 }
 
 // fp32 pools: the step of one split of a unit's rows by one wavefront, over
@@ -2196,104 +2542,23 @@ __global__ __launch_bounds__(NW * 64) void k_prompt_select_mfma(LayerView L, Ste
     }
 }
 
-// Epilogue kernel of the split path: the retention policy on the scores the
-// step kernel wrote, and the merge of the splits' partial attention
-// (out = sum_s 2^(M_s - M) O_s / sum_s 2^(M_s - M) L_s); then the state goes
-// out. One workgroup per decision: L.hgrp units (the KV heads of a sequence
-// when they share one page table, whose slot states are then identical), a
-// page's score aggregating the bounds of all their heads. The refresh runs
-// on the whole workgroup; wavefront 0 then evicts while the others start
-// the merge. merge 0: the step kernel wrote the outputs (bf16, one
-// workgroup per unit).
-template <typename T>
-__global__ __launch_bounds__(1024) void k_epilogue(LayerView L, StepIO io, double r, int merge) {
+// Epilogue kernel of the fp32 pools' split path: the rest of the step
+// (finish_units) once the step kernel's launch has ended. One workgroup per
+// decision.
+__global__ __launch_bounds__(1024) void k_epilogue_f32(LayerView L, StepIO io, double r) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ RetShared ret;
-    __shared__ int s_aux[260];
-    const int S = L.S, G = L.G, D = L.D, nsplit = L.nsplit, nu = L.hgrp;
-    const int tid = threadIdx.x, nth = blockDim.x;
-    double* s_score = reinterpret_cast<double*>(smem);
-    double* s_mz = s_score + S;  // [nu*G][2], softmax aggregation only
-    float* s_ml = reinterpret_cast<float*>(s_mz + (L.agg ? 2 * (size_t)nu * G : 0));  // [nsplit][G][2], merge
-    float* s_den = s_ml + (merge ? 2 * (size_t)nsplit * G : 0);                       // [G], merge
-    int* s_state = reinterpret_cast<int*>(s_den + (merge ? G : 0));
-    int* s_ts = s_state + S;
-    int* s_lid = s_ts + S;
-    const int u0 = blockIdx.x * nu;
+    __shared__ int s_aux[261];
+    const int nu = L.hgrp, u0 = blockIdx.x * nu, tid = threadIdx.x, nth = blockDim.x;
     if (io.active != nullptr && io.active[u0 / L.nkv] == 0) return;
-    const size_t base = (size_t)u0 * S;
-    // The first pass's reads go out together with the slots': the page
-    // score of slot tid (max over the units; read whether or not the page
-    // turns out to be ranked) and the first unit's running maximum and sum
-    // of item tid of the merge.
-    double sc_first = -INFINITY;
-    if (!L.agg && tid < S) {
-        sc_first = L.score[base + tid];
-#pragma unroll 8
-        for (int h = 1; h < nu; ++h) sc_first = fmax(sc_first, L.score[base + (size_t)h * S + tid]);
-    }
-    float m_first = 0.0f, l_first = 0.0f;
-    if (merge && tid < nsplit * G) {
-        const float* pf = L.part + (size_t)u0 * nsplit * G * (D + 2) + (size_t)tid * (D + 2);
-        m_first = pf[D];
-        l_first = pf[D + 1];
-    }
-    const UnitRec ur = read_unit(L, u0);
-    load_slots(L, u0, ur, s_score, s_state, s_ts, s_lid);
-    __syncthreads();
-    if (!L.agg) {
-        if (tid < S && ranked(L, s_state[tid])) s_score[tid] = sc_first;
-        for (int s = tid + nth; s < S; s += nth)
-            if (ranked(L, s_state[s])) {
-                double best = L.score[base + s];
-#pragma unroll 8
-                for (int h = 1; h < nu; ++h) best = fmax(best, L.score[base + (size_t)h * S + s]);
-                s_score[s] = best;
-            }
-    }
-    __syncthreads();
-    if (L.agg) softmax_sum_block(L, L.score + base * G, nu, s_state, s_score, s_mz, tid, nth);
-    refresh_block(L, ur, r, s_score, s_state, s_ts, s_aux, tid, nth, L.dbase);
-    __syncthreads();
-    if (tid < 64) evict_wave(L, ur, s_state, s_ts, s_lid, ret);
-    for (int uh = 0; merge && uh < nu; ++uh) {
-        const int u = u0 + uh;
-        const float* pu = L.part + (size_t)u * nsplit * G * (D + 2);
-        // every split's running max and sum, then per head the weights' sum
-        if (uh == 0 && tid < nsplit * G) {
-            s_ml[2 * tid] = m_first;
-            s_ml[2 * tid + 1] = l_first;
-        }
-        for (int i = uh == 0 ? tid + nth : tid; i < nsplit * G; i += nth) {
-            s_ml[2 * i] = pu[(size_t)i * (D + 2) + D];
-            s_ml[2 * i + 1] = pu[(size_t)i * (D + 2) + D + 1];
-        }
+    for (int uh = 0; nu > 1 && uh < nu; ++uh) {
+        const MergeFirst mf = merge_first(L, u0 + uh, tid);
+        merge_stage(L, u0 + uh, mf, reinterpret_cast<float*>(smem), tid, nth);
         __syncthreads();
-        for (int h = tid; h < G; h += nth) {
-            float M = -INFINITY;
-            for (int s = 0; s < nsplit; ++s) M = fmaxf(M, s_ml[2 * (s * G + h)]);
-            float Ls = 0.0f;
-            for (int s = 0; s < nsplit; ++s) {
-                const float ms = s_ml[2 * (s * G + h)];
-                const float wt = (ms == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(ms - M);
-                s_ml[2 * (s * G + h)] = wt;  // the split's weight replaces its max
-                Ls += wt * s_ml[2 * (s * G + h) + 1];
-            }
-            s_den[h] = Ls;
-        }
-        __syncthreads();
-        for (int idx = tid; idx < G * D; idx += nth) {
-            const int h = idx / D, c = idx - (idx / D) * D;
-            float O = 0.0f;
-#pragma unroll 4
-            for (int s = 0; s < nsplit; ++s) O += s_ml[2 * (s * G + h)] * pu[((size_t)s * G + h) * (D + 2) + c];
-            ((T*)io.out)[((size_t)u * G + h) * D + c] = from_f<T>(O / s_den[h]);
-        }
+        merge_out<float>(L, io, u0 + uh, mf, reinterpret_cast<float*>(smem), tid, nth);
         __syncthreads();
     }
-    __syncthreads();
-    for (int uh = 0; uh < nu; ++uh)
-        retention_store(L, io, u0 + uh, ur, s_state, s_ts, s_lid, ret, tid, nth);
+    finish_units<float>(L, io, r, u0, nu, nu == 1, smem, s_aux, ret, tid, nth);
 }
 
 inline unsigned grid1d(size_t n, int block) { return (unsigned)((n + block - 1) / block); }
@@ -2307,66 +2572,116 @@ size_t step_lds(int G, int D, int S, int NW, bool fused, int agg, int list_ints)
     return b + (size_t)list_ints * 4;
 }
 
-template <int D, int NW, bool AGG, int LM, bool NT = false>
-void launch_step_inst(const LayerView& L, const StepIO& io, const StepPlan& pl, float sl2, double r,
-                      hipStream_t s) {
-    hipLaunchKernelGGL((k_step_bf16<D, NW, AGG, LM, NT>), dim3((unsigned)(L.U * pl.nsplit)), dim3(NW * 64),
-                       pl.lds, s, L, io, sl2, r, pl.fused ? 1 : 0);
+// Every instance of the bf16 step kernel for one head_dim and workgroup size.
+// f(pointer, ...) is called for the one that the layer and plan ask for, or
+// (all) for each.
+template <int D, int NW, class F>
+void each_step_bf16(bool all, bool agg, int lm, bool nt, bool split, F&& f) {
+    auto one = [&](auto A, auto M, auto N, auto P) {
+        if (all || (agg == A.value && lm == M.value && nt == N.value && split == P.value))
+            f(k_step_bf16<D, NW, A.value, M.value, N.value, P.value>);
+    };
+    auto nts = [&](auto A, auto M, auto P) {
+        one(A, M, std::false_type{}, P);
+        one(A, M, std::true_type{}, P);
+    };
+    const std::integral_constant<int, 0> m0{};
+    const std::integral_constant<int, 1> m1{};
+    const std::integral_constant<int, 2> m2{};
+    const std::true_type yes{};
+    const std::false_type no{};
+    nts(no, m0, no);
+    nts(no, m0, yes);
+    nts(no, m1, yes);  // (a fused plan without the softmax aggregation selects in the step)
+    nts(no, m2, no);
+    nts(yes, m0, no);
+    nts(yes, m0, yes);
+    nts(yes, m1, no);
+    nts(yes, m1, yes);
 }
+
+}  // namespace
 
 template <int D, int NW>
 hipError_t launch_step_bf16(const LayerView& L, const StepIO& io, const StepPlan& pl, float sl2, double r,
                             hipStream_t s) {
-    const bool list = L.topk >= 0;
-    if (L.agg) {
-        if (list && L.nt) launch_step_inst<D, NW, true, 1, true>(L, io, pl, sl2, r, s);
-        else if (list) launch_step_inst<D, NW, true, 1>(L, io, pl, sl2, r, s);
-        else if (L.nt) launch_step_inst<D, NW, true, 0, true>(L, io, pl, sl2, r, s);
-        else launch_step_inst<D, NW, true, 0>(L, io, pl, sl2, r, s);
-    } else {
-        if (pl.select_in_step && L.nt) launch_step_inst<D, NW, false, 2, true>(L, io, pl, sl2, r, s);
-        else if (pl.select_in_step) launch_step_inst<D, NW, false, 2>(L, io, pl, sl2, r, s);
-        else if (list && L.nt) launch_step_inst<D, NW, false, 1, true>(L, io, pl, sl2, r, s);
-        else if (list) launch_step_inst<D, NW, false, 1>(L, io, pl, sl2, r, s);
-        else if (L.nt) launch_step_inst<D, NW, false, 0, true>(L, io, pl, sl2, r, s);
-        else launch_step_inst<D, NW, false, 0>(L, io, pl, sl2, r, s);
-    }
+    const int lm = pl.select_in_step ? 2 : L.topk >= 0 ? 1 : 0;
+    each_step_bf16<D, NW>(false, L.agg != 0, lm, L.nt != 0, !pl.fused, [&](auto* kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(L.U * pl.nsplit)), dim3(NW * 64), pl.lds, s, L, io, sl2, r);
+    });
     return hipGetLastError();
 }
 
 template <int D, int NW>
 hipError_t allow_lds_all(int bytes) {
     hipError_t e = hipSuccess;
-    auto set = [&](const void* f) {
-        hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    each_step_bf16<D, NW>(true, false, 0, false, false, [&](auto* kernel) {
+        hipError_t r = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (r != hipSuccess) e = r;
-    };
-    set((const void*)k_step_bf16<D, NW, false, 0>);
-    set((const void*)k_step_bf16<D, NW, true, 0>);
-    set((const void*)k_step_bf16<D, NW, false, 1>);
-    set((const void*)k_step_bf16<D, NW, true, 1>);
-    set((const void*)k_step_bf16<D, NW, false, 2>);
-    set((const void*)k_step_bf16<D, NW, false, 0, true>);
-    set((const void*)k_step_bf16<D, NW, false, 2, true>);
-    set((const void*)k_step_bf16<D, NW, true, 0, true>);
-    set((const void*)k_step_bf16<D, NW, false, 1, true>);
-    set((const void*)k_step_bf16<D, NW, true, 1, true>);
+    });
     return e;
 }
 
-}  // namespace
+// This file is compiled once for each RAAS_PART (in parallel): parts 1 to 6
+// hold the instances of the bf16 step kernel, part 0 everything else.
+#if RAAS_PART == 0
+#define RAAS_STEP(D, NW)                                                                                        \
+    extern template hipError_t launch_step_bf16<D, NW>(const LayerView&, const StepIO&, const StepPlan&, float, \
+                                                       double, hipStream_t);                                    \
+    extern template hipError_t allow_lds_all<D, NW>(int);
+RAAS_STEP(128, 8)
+RAAS_STEP(128, 4)
+RAAS_STEP(128, 2)
+RAAS_STEP(64, 8)
+RAAS_STEP(64, 4)
+RAAS_STEP(64, 2)
+#else
+#define RAAS_STEP(D, NW)                                                                                         \
+    template hipError_t launch_step_bf16<D, NW>(const LayerView&, const StepIO&, const StepPlan&, float, double, \
+                                                hipStream_t);                                                    \
+    template hipError_t allow_lds_all<D, NW>(int);
+#if RAAS_PART == 1
+RAAS_STEP(128, 8)
+#elif RAAS_PART == 2
+RAAS_STEP(128, 4)
+#elif RAAS_PART == 3
+RAAS_STEP(128, 2)
+#elif RAAS_PART == 4
+RAAS_STEP(64, 8)
+#elif RAAS_PART == 5
+RAAS_STEP(64, 4)
+#elif RAAS_PART == 6
+RAAS_STEP(64, 2)
+#endif
+#endif
 
+#if RAAS_PART == 0
 // ---------------------------------------------------------------------------
 
-// Blocks per wavefront up to which one fused workgroup per unit is chosen
-// over a split (measured at batch 1 and 4, 32 blocks per unit over 8
-// wavefronts: 14.6 against 19.2 us and 15.9 against 19.7 us per step), and
-// up to kFusedBlocksPerWaveFewSlots with at most kFewSlots slots, where the
-// fused workgroup's retention (one wavefront counting over all slots) is
-// short: 64 blocks and 64 slots at batch 1, 4 and 8, the fused kernel
-// 17.1, 17.4 and 18.0 us against 17.6, 18.6 and 20.4 us for the split
-// path's two kernels before their second launch; with 128 slots (page 16)
-// fused took 22.0 against 20.3 us per step at batch 4.
+// One fused workgroup per unit, or the unit's blocks split over several
+// workgroups, the last of which finishes the step. A split workgroup pays for
+// its start and for publishing (about 8 us, of which the last one's finish is
+// 4), so splits pay only where they put idle CUs to work, in one round:
+// 256 / U workgroups per unit at most, and none from 129 units on (192 units,
+// L 2048: 42.7 us fused, 59.1 in two; 192 units, L 8192: 118 against 137 to
+// 163 at any split). Below, a unit is split when it has more blocks than
+// kFusedBlocks (us per step, page 16, sixteen pools in turn so that none is
+// cached, fused against split: 8 units, 32 blocks 14.4 / 14.5, 64 blocks 19.7 /
+// 15.1; 32 units, 32 blocks 17.1 / 16.8, 48 blocks 23.6 / 18.9, 64 blocks 28.2
+// / 19.8; 64 units, 32 blocks 19.4 / 19.8, 48 blocks 25.2 / 22.9, 64 blocks
+// 30.3 / 24.7; 96 units, 64 blocks 33.6 / 31.0); from kHalfUnits on, where
+// two workgroups per unit fill the chip, when it has more than
+// kFusedBlocksHalf (128 units: 64 blocks 34.4 / 35.9, 128 blocks 60.6 / 59.5,
+// 256 blocks 95.4 / 91.1). More than kSplits splits, or fewer than 8 blocks in
+// one, no longer help (8 units: 64 blocks 15.1 in 8 and 15.3 in 16; 256 blocks
+// 26.1 in 4, 21.3 in 8, 19.2 in 16, 21.0 in 32).
+constexpr int kFusedBlocks = 32;
+constexpr int kHalfUnits = 113;
+constexpr int kFusedBlocksHalf = 64;
+constexpr int kSplits = 16;
+// Steps whose scratch is the fixed array (raas_decode_step_static) keep the
+// plans that need none up to this many blocks per wavefront, or, in pools of
+// at most kFewSlots slots, kFusedBlocksPerWaveFewSlots.
 constexpr int kFusedBlocksPerWave = 6;
 constexpr int kFusedBlocksPerWaveFewSlots = 8;
 constexpr int kFewSlots = 64;
@@ -2374,10 +2689,8 @@ constexpr int kFewSlots = 64;
 // attended blocks per wavefront and prompt pages (batch 1 and 8, 128 prompt
 // pages, 72 attended blocks over 8 wavefronts: 30.3 against 36.2 and 32.2
 // against 36.2 us per step; batch 4, 512 pages, 80 blocks: 44.0 against
-// 54.4 us, the fused kernel 40.1 us and the split path's four kernels 37.5
-// to 39.1 us before their launch gaps; at 1024 prompt pages the fused
-// workgroup's own bound intervals cost more than the split path's
-// kernels: 68.8 against 45.9 us at batch 1).
+// 54.4 us; at 1024 prompt pages the fused workgroup's own bound intervals cost
+// more than the split path's kernels: 68.8 against 45.9 us at batch 1).
 constexpr int kFusedPromptBlocksPerWave = 12;
 constexpr int kFusedPromptPages = 512;
 
@@ -2389,7 +2702,8 @@ constexpr int kSmallWorkUnits = 1024;
 constexpr int kSmallWorkBlocks = 32;
 
 StepPlan plan_step(int U, int G, int D, int S, int Lcap, int ps, int work_blocks, bool bf16, int agg,
-                   bool grouped, int list_ints, int split_override, int npr) {
+                   bool grouped, int list_ints, int split_override, int npr, int nkv,
+                   bool fixed_scratch) {
     (void)ps;
     StepPlan pl{};
     const int nblk = Lcap / kBlockTokens;
@@ -2405,38 +2719,37 @@ StepPlan plan_step(int U, int G, int D, int S, int Lcap, int ps, int work_blocks
                 break;
             }
         }
-        // two or more units per CU: workgroups of 4 wavefronts, two per CU,
-        // so that one unit's serial phases (staging, selection, retention)
-        // overlap another's streaming
-        if (split_override <= 0 && !grouped && U >= 512 && pl.waves == 8 &&
-            2 * step_lds(G, D, S, 4, true, agg, list_ints) <= kMaxLds)
+        // more units than CUs: workgroups of 4 wavefronts, two per CU, so that
+        // one unit's serial phases (staging, selection, retention) overlap
+        // another's streaming, and up to 512 units run in one round (288 units,
+        // L 1024: 45.4 -> 39.0 us; 352 units, L 8192: 254 -> 242; 504 units,
+        // L 2048: 90.5 -> 87.5)
+        if (split_override <= 0 && U > 256 && pl.waves == 8 &&
+            2 * step_lds(G, D, S, 4, !grouped, agg, list_ints) <= kMaxLds)
             pl.waves = 4;
         // four or more units per CU, each with little to stream: four
         // workgroups per CU overlap more units' serial phases
         if (split_override <= 0 && !grouped && U >= kSmallWorkUnits && work_blocks <= kSmallWorkBlocks &&
             pl.waves == 4 && 4 * step_lds(G, D, S, 2, true, agg, list_ints) <= kMaxLds)
             pl.waves = 2;
+        const bool fits = !grouped && step_lds(G, D, S, pl.waves, true, agg, list_ints) <= kMaxLds;
+        const int fused_blocks = U < kHalfUnits ? kFusedBlocks : kFusedBlocksHalf;
         if (split_override > 0) {
             want = split_override;
-        } else if (!grouped &&
+        } else if (fits && fixed_scratch &&
                    (nblk <= kFusedBlocksPerWave * pl.waves ||
-                    (S <= kFewSlots && nblk <= kFusedBlocksPerWaveFewSlots * pl.waves)) &&
-                   step_lds(G, D, S, pl.waves, true, agg, list_ints) <= kMaxLds) {
-            // few blocks per wavefront: one workgroup per unit, which also runs
-            // the epilogue, beats spreading the unit over more CUs and paying a
-            // second launch (about 10 us) for the merge
+                    (S <= kFewSlots && nblk <= kFusedBlocksPerWaveFewSlots * pl.waves))) {
             want = 1;
-        } else if (!grouped && list_ints > 0 && !agg && U < 256 && npr <= kFusedPromptPages &&
-                   work_blocks <= kFusedPromptBlocksPerWave * pl.waves &&
-                   step_lds(G, D, S, pl.waves, true, agg, list_ints) <= kMaxLds) {
+        } else if (fits && list_ints > 0 && !agg && U < 256 && npr <= kFusedPromptPages &&
+                   work_blocks <= kFusedPromptBlocksPerWave * pl.waves) {
             // a short prompt region: the fused workgroup chooses its prompt
             // pages itself and attends the chosen blocks and the decode ones,
             // which saves the selection kernel's launch as well
             want = 1;
+        } else if (fits && work_blocks <= fused_blocks && (list_ints == 0 || agg || npr <= kFusedPromptPages)) {
+            want = 1;
         } else {
-            // one workgroup per CU over the 256 CUs
-            const double per_wave = fmax(1.0, (double)U * nblk / (256.0 * pl.waves));
-            want = (int)ceil(nblk / (pl.waves * per_wave) - 1e-9);
+            want = std::min(std::min(std::max(256 / U, 1), kSplits), (work_blocks + 7) / 8);
         }
     }
     want = want < 1 ? 1 : want;
@@ -2445,8 +2758,14 @@ StepPlan plan_step(int U, int G, int D, int S, int Lcap, int ps, int work_blocks
     pl.bps = (nblk + want - 1) / want;
     pl.nsplit = (nblk + pl.bps - 1) / pl.bps;
     if (bf16) {
-        pl.fused = !grouped && pl.nsplit == 1 && step_lds(G, D, S, pl.waves, true, agg, list_ints) <= kMaxLds;
+        // (fused, a step with fewer units than CUs would bound a long prompt
+        // region on one CU per unit: the selection kernels do that faster)
+        const bool long_prompt = list_ints > 0 && !agg && U < 256 && npr > kFusedPromptPages;
+        pl.fused = !grouped && !long_prompt && pl.nsplit == 1 &&
+                   step_lds(G, D, S, pl.waves, true, agg, list_ints) <= kMaxLds;
         pl.lds = step_lds(G, D, S, pl.waves, pl.fused, agg, list_ints);
+        // (the workgroup that finishes a split unit reuses the step's LDS)
+        if (!pl.fused) pl.lds = std::max(pl.lds, finish_lds(G, S, pl.nsplit, agg, grouped ? nkv : 1));
     } else {
         // fp32: one workgroup per unit with a wavefront per split (up to 8,
         // two per SIMD at the kernel's registers), which then runs the
@@ -2598,16 +2917,12 @@ hipError_t launch_step(const LayerView& L, const StepIO& io, const StepPlan& pl,
 }
 
 hipError_t launch_epilogue(const LayerView& L, const StepIO& io, double r, hipStream_t stream) {
-    const int merge = !(L.bf16 && L.nsplit == 1);  // else the step kernel wrote the outputs
-    const size_t shm = (size_t)L.S * (8 + 12) + (L.agg ? (size_t)L.hgrp * L.G * 16 : 0) +
-                       (merge ? ((size_t)2 * L.nsplit * L.G + L.G) * 4 : 0);
     const dim3 grid((unsigned)(L.U / L.hgrp));
     const dim3 block(grid.x < 256 ? 1024 : 256);  // fewer workgroups than CUs: more threads each
-    if (L.bf16)
-        hipLaunchKernelGGL(k_epilogue<uint16_t>, grid, block, shm, stream, L, io, r, merge);
-    else
-        hipLaunchKernelGGL(k_epilogue<float>, grid, block, shm, stream, L, io, r, merge);
+    hipLaunchKernelGGL(k_epilogue_f32, grid, block, finish_lds(L.G, L.S, L.nsplit, L.agg, L.hgrp), stream, L, io, r);
     return hipGetLastError();
 }
+
+#endif  // RAAS_PART == 0
 
 }  // namespace raas

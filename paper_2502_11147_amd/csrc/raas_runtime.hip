@@ -61,6 +61,7 @@ struct raas_pool {
     int32_t* unit = nullptr;  // [Ly][U][kUnitFields]
     int32_t* err = nullptr;
     float* part = nullptr;    // [U][splits][G][D+2], scratch of one step
+    int32_t* arrived = nullptr;  // [2][U] arrival counters of the split units and shared decisions, zero between steps
     double* score = nullptr;  // [U][S] page scores, or [U][S][G] per-head bounds, scratch of one step
     int32_t* fill_att = nullptr;  // [U][S] fills the attention sees (prompt selection), scratch of one step
     int32_t* blist = nullptr;     // [U][Lcap/32] blocks a step visits (prompt selection), likewise
@@ -119,6 +120,7 @@ LayerView view(const raas_pool* p, int layer) {
     L.err = p->err;
     L.score = p->score;
     L.part = p->part;
+    L.arrived = p->arrived;
     L.rev = 0;
     L.nsplit = 1;
     L.bps = p->Lcap / kBlockTokens;
@@ -300,7 +302,8 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
     }
     const StepPlan pl = plan_step(p->U, p->G, p->D, p->S, L.nblk * kBlockTokens, p->ps, work_blocks,
                                   p->cfg.dtype == RAAS_BF16, p->cfg.score_aggregation,
-                                  p->cfg.decision_scope == RAAS_SCOPE_SEQUENCE, list_ints(p), p->split_override, p->npr);
+                                  p->cfg.decision_scope == RAAS_SCOPE_SEQUENCE, list_ints(p), p->split_override, p->npr,
+                                  p->cfg.n_kv_heads, fixed_scratch);
     L.nsplit = pl.nsplit;
     L.bps = pl.bps;
     // the first score pass issued with the first blocks: the score barrier and
@@ -308,7 +311,7 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
     // wavefronts streams at least 8 blocks each (batch 32 at L 2048: 40.79 ->
     // 40.38 us, the Qwen stack and L 8192 level) and not below (batch 1 at
     // L 1024 +0.14 us; batch 128 at L 512, 2 wavefronts, +0.23 us)
-    L.early = pl.waves == 8 && L.nblk >= 8 * pl.waves ? 1 : 0;
+    L.early = pl.waves == 8 && (pl.nsplit > 1 || L.nblk >= 8 * pl.waves) ? 1 : 0;
     const bool select_kernel = p->npr > 0 && !pl.select_in_step;
     if (fixed_scratch) {
         const size_t U = (size_t)p->U, S = (size_t)p->S;
@@ -361,7 +364,7 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
     hipError_t e = launch_step(L, io, pl, p->cfg.r, s);
     if (prof) prof_record(p, 0, false, s);
     if (e != hipSuccess) return hip_fail(e, "step launch");
-    if (!pl.fused) {
+    if (!pl.fused && p->cfg.dtype != RAAS_BF16) {
         if (prof) prof_record(p, 1, true, s);
         e = launch_epilogue(L, io, p->cfg.r, s);
         if (prof) prof_record(p, 1, false, s);
@@ -428,6 +431,7 @@ raas_status raas_create_pool(const raas_config* cfg, void* stream, raas_pool** o
         {(void**)&p->part, (size_t)p->U * max_split * p->G * (p->D + 2) * sizeof(float)},
         {(void**)&p->score,
          (size_t)p->U * p->S * (cfg->score_aggregation == RAAS_SCORE_SOFTMAX_SUM ? p->G : 1) * sizeof(double)},
+        {(void**)&p->arrived, 2 * (size_t)p->U * sizeof(int32_t)},
         {(void**)&p->seqbuf, 2 * (size_t)cfg->batch * sizeof(int32_t)},
         {(void**)&p->fill_att, p->npr > 0 ? (size_t)p->U * p->S * sizeof(int32_t) : 4},
         {(void**)&p->blist, p->npr > 0 ? (size_t)p->U * (p->Lcap / kBlockTokens) * sizeof(int32_t) : 4},
@@ -484,7 +488,7 @@ void raas_destroy(raas_pool* p) {
             if (ev) (void)hipEventDestroy(ev);
     }
     void* ptrs[] = {p->K,     p->V,     p->kmin,  p->kmax,     p->meta,  p->unit, p->err,
-                    p->part,  p->score, p->seqbuf, p->fill_att, p->blist, p->bcnt, p->pivl};
+                    p->part,  p->arrived, p->score, p->seqbuf, p->fill_att, p->blist, p->bcnt, p->pivl};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     if (p->seqhost) (void)hipHostFree(p->seqhost);

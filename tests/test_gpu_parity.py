@@ -520,6 +520,37 @@ def test_score_variants_full_size(name, steps, units, splits):
     assert rep.evictions > 0
 
 
+# Units split over several workgroups, the last of which finishes the step:
+# ranked slots at the edges of its counting ranges (64, 128, 256; odd and even
+# slot counts), more splits than the merge reads ahead (16), and the softmax
+# aggregation's bounds staged in LDS or too many for that.
+FINISH_CASES = [
+    dict(budget=8 * 64, splits=2),
+    dict(budget=8 * 65, splits=16),
+    dict(budget=8 * 128, splits=17),
+    dict(budget=8 * 129, splits=3),
+    dict(budget=8 * 256, splits=2),
+    dict(budget=8 * 257, splits=2),
+    dict(budget=8 * 65, splits=3, scope=1),
+    dict(budget=8 * 64, splits=2, aggregation=1),
+    dict(budget=8 * 530, splits=2, aggregation=1, prefill_len=8 * 470, n_q_heads=32),  # G 16: 68 KB of bounds
+    dict(budget=8 * 40, splits=17, scope=1, aggregation=1),
+    dict(budget=8 * 65, splits=3, head_dim=64, n_q_heads=28, n_kv_heads=4),
+]
+
+
+@pytest.mark.parametrize("case", FINISH_CASES, ids=[",".join("%s=%s" % kv for kv in c.items()) for c in FINISH_CASES])
+def test_split_unit_finish(case):
+    case = dict(case)
+    run_kw = {k: case.pop(k) for k in ("splits", "aggregation", "scope") if k in case}
+    prompt = case.pop("prefill_len", 5)
+    w = small(page_size=8, prefill_len=prompt, decode_steps=case["budget"] - prompt + 24, **case)
+    _say("case split finish %s %s steps %d" % (case, run_kw, w.decode_steps))
+    rep = run_parity(w, seed=21, steps=w.decode_steps, out_every=4, **run_kw)
+    _report(rep, "split-finish")
+    assert rep.evictions > 0
+
+
 # One page table per (sequence, layer) shared by its KV heads (decision
 # scope 1), against the oracle's grouped step; (aggregation, rank_pinned).
 SCOPE_VARIANTS = [(0, False), (1, False), (0, True)]
