@@ -198,8 +198,9 @@ raas_status raas_decode_step_masked(raas_pool* pool, int32_t layer, const void* 
 /* raas_decode_step for callers that cannot allocate device memory (code
  * under HIP graph capture, serving loops or harnesses that forbid
  * hipMalloc): the same kernels and results, but the step's scratch memory
- * -- the partial attention of split units, the page scores handed to the
- * epilogue kernel, and the prompt selection's fills and block lists -- lies
+ * -- the partial attention of split units, the page scores that their
+ * workgroups hand to the last one, and the prompt selection's fills and block
+ * lists -- lies
  * in a fixed array of RAAS_STATIC_SCRATCH_BYTES in the library's device
  * code instead of the pool's own buffers. The call allocates nothing and
  * records no profiling events. Steps whose plan needs no scratch (one
@@ -262,10 +263,9 @@ raas_status raas_set_attention_splits(raas_pool* pool, int32_t splits);
 
 /* Kernel timing with HIP events recorded on the call's stream around each
  * enabled kernel of raas_decode_step. mask bit i enables kernel i:
- * 0 the step kernel (attention, append, page scores, and the epilogue when a
- * single workgroup covers a unit), 1 the epilogue kernel (split merge,
- * refresh, eviction; launched when a unit is split over several
- * workgroups, for fp32 pools and for the sequence scope), 2 the prompt
+ * 0 the step kernel (the whole step but for the prompt selection: the last
+ * workgroup of a unit that is split over several finishes it), 1 no kernel
+ * (kept for callers that read it: it counts no launches), 2 the prompt
  * selection kernel (with a prompt region, when the step kernel does not
  * select the prompt pages itself: split plans, the softmax aggregation and
  * fp32 pools). mask 0 turns timing off.

@@ -19,7 +19,7 @@ PREFILL_PIN_HEAD, PREFILL_ERROR = 0, 1
 SCORE_MAX, SCORE_SOFTMAX_SUM = 0, 1
 SCOPE_KV_HEAD, SCOPE_SEQUENCE = 0, 1
 FREE, PINNED, EVICTABLE = 0, 1, 2
-KERNELS = ("step", "epilogue", "prompt_select")  # raas_profile kernel indices
+KERNELS = ("step", "epilogue", "prompt_select")  # raas_profile kernel indices (no launches under "epilogue")
 
 # C entry points declared in include/raas.h
 EXPORTS = (

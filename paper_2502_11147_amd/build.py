@@ -15,7 +15,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB_PATH = os.path.join(HERE, "libraas.so")
 KERNELS = os.path.join(CSRC, "raas_kernels.hip")
 # translation units of libraas.so: the kernels' file once per RAAS_PART, and the runtime
-KERNEL_PARTS = 7
+KERNEL_PARTS = 15
 UNITS = [(KERNELS, ["-DRAAS_PART=%d" % i]) for i in range(KERNEL_PARTS)] + [(os.path.join(CSRC, "raas_runtime.hip"), [])]
 # the streaming probe (measurement only) is a library of its own
 PROBE_SOURCES = [os.path.join(CSRC, "raas_probe.hip")]

@@ -99,7 +99,7 @@ struct StepPlan {
 // the epilogue kernel;
 // list_ints: LDS ints of a block list or of the in-step prompt selection (0
 // without a prompt region); fixed_scratch: raas_decode_step_static
-StepPlan plan_step(int U, int G, int D, int S, int Lcap, int ps, int work_blocks, bool bf16, int agg,
+StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool bf16, int agg,
                    bool grouped, int list_ints, int split_override,
                    int npr, int nkv, bool fixed_scratch);
 // Quest on the prompt pages: the attended fills and the block list of a step.
@@ -114,8 +114,5 @@ hipError_t launch_prefill(const LayerView& L, const void* k, const void* v, cons
 // The step kernel: the whole step (bf16 and fused fp32 plans), or attention, page scores and append.
 hipError_t launch_step(const LayerView& L, const StepIO& io, const StepPlan& plan, double r,
                        hipStream_t stream);
-// The epilogue kernel of the fp32 split path: merge, refresh, evict, state
-// out; one workgroup per group of L.hgrp units.
-hipError_t launch_epilogue(const LayerView& L, const StepIO& io, double r, hipStream_t stream);
 
 }  // namespace raas

@@ -82,6 +82,14 @@ __device__ __forceinline__ uint16_t u16_at(const u32x4& x, int e) {
     return (uint16_t)((x[e >> 1] >> ((e & 1) * 16)) & 0xFFFFu);
 }
 
+// element e of a 16-byte vector of T, as fp32
+template <typename T>
+__device__ __forceinline__ float vec_elem(const u32x4& x, int e);
+template <>
+__device__ __forceinline__ float vec_elem<uint16_t>(const u32x4& x, int e) { return bf2f(u16_at(x, e)); }
+template <>
+__device__ __forceinline__ float vec_elem<float>(const u32x4& x, int e) { return __uint_as_float(x[e]); }
+
 // ---------------------------------------------------------------------------
 // Prefill (the prefill stage of Algorithm 1's cache store): a unit's first
 // tokens go to pages 0, 1, ..., which are marked pinned; at most S-1 pages
@@ -302,7 +310,7 @@ __device__ __forceinline__ bool arrive_last(int32_t* counter, int total, int* s_
 // ---------------------------------------------------------------------------
 // Page scores (Section 3.3, Quest's representative keys): for each evictable
 // page, max over the G query heads of sum_c max(q_c*kmax_c, q_c*kmin_c),
-// summed in fp64. A product of two bf16 values has at most 16 significant
+// summed in fp64. bf16 pools: a product of two bf16 values has at most 16 significant
 // bits, so both products are formed exactly in fp32 (q and the keys are
 // staged as fp32), the larger is widened and added in fp64: each add rounds
 // exactly as the fp64 sum of the exact product (products below fp32's normal
@@ -335,27 +343,18 @@ __device__ __forceinline__ float max_xor16_32(float x) {
     const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
     return fmaxf(__builtin_bit_cast(float, (unsigned)b[0]), __builtin_bit_cast(float, (unsigned)b[1]));
 }
-// Whole-wavefront max and sum of a float with no LDS round trip: lane ^ 1
-// and lane ^ 2 by quad permutes, then the mirrors within 8 and within 16
-// lanes (every lane of a quad, then of an 8-lane half, holds the same value
-// by then), then the two permlane swaps. Every lane ends with the result,
-// the sum in the same order on every lane.
+// DPP move of a float; 0x124 and 0x128 (row_ror 4 and 8) turn the 16 lanes of
+// a row, so that two steps with each reach the lanes equal in lane & 3.
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
 }
-__device__ __forceinline__ float wave_max_dpp(float x) {
-    x = fmaxf(x, dpp_f32<0xB1>(x));
-    x = fmaxf(x, dpp_f32<0x4E>(x));
-    x = fmaxf(x, dpp_f32<0x141>(x));
-    x = fmaxf(x, dpp_f32<0x140>(x));
-    return max_xor16_32(x);
+__device__ __forceinline__ float sum_ror4_8(float x) {
+    x += dpp_f32<0x124>(x);
+    return x + dpp_f32<0x128>(x);
 }
-__device__ __forceinline__ float wave_sum_dpp(float x) {
-    x += dpp_f32<0xB1>(x);
-    x += dpp_f32<0x4E>(x);
-    x += dpp_f32<0x141>(x);
-    x += dpp_f32<0x140>(x);
+// sum over lanes i, i ^ 16, i ^ 32 and i ^ 48, in the same order on each
+__device__ __forceinline__ float sum_xor16_32(float x) {
     const unsigned u = __builtin_bit_cast(unsigned, x);
     const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
     x = __builtin_bit_cast(float, (unsigned)a[0]) + __builtin_bit_cast(float, (unsigned)a[1]);
@@ -375,38 +374,46 @@ __device__ __forceinline__ int qpad_index(int i) {
     return h * qpad_row(D) + c + 4 * (c / (D / 8));
 }
 
-template <int D>
+template <typename T, int D>
 struct ScoreFrag {
-    static constexpr int SV = D / 64;  // 16-byte vectors per array per lane (D/8 bf16 channels)
+    static constexpr int SV = D * (int)sizeof(T) / 128;  // 16-byte vectors per array per lane (D/8 channels)
     u32x4 kx[SV], kn[SV];
 };
 
-template <int D>
+template <typename T, int D>
 __device__ __forceinline__ void score_issue(const LayerView& L, int u, int p, int part, bool load,
-                                            ScoreFrag<D>& f) {
+                                            ScoreFrag<T, D>& f) {
+    constexpr int V = 16 / sizeof(T);
     const size_t off = ((size_t)u * L.S + p) * D + part * (D / 8);
-    const uint16_t* kx = (const uint16_t*)L.kmax + off;
-    const uint16_t* kn = (const uint16_t*)L.kmin + off;
+    const T* kx = (const T*)L.kmax + off;
+    const T* kn = (const T*)L.kmin + off;
 #pragma unroll
-    for (int i = 0; i < ScoreFrag<D>::SV; ++i) {
-        f.kx[i] = load ? ld4(kx + 8 * i) : u32x4{0u, 0u, 0u, 0u};
-        f.kn[i] = load ? ld4(kn + 8 * i) : u32x4{0u, 0u, 0u, 0u};
+    for (int i = 0; i < ScoreFrag<T, D>::SV; ++i) {
+        f.kx[i] = load ? ld4(kx + V * i) : u32x4{0u, 0u, 0u, 0u};
+        f.kn[i] = load ? ld4(kn + V * i) : u32x4{0u, 0u, 0u, 0u};
     }
 }
 
-template <int D>
+template <typename T, int D>
 __device__ __forceinline__ double score_finish(const LayerView& L, int u, int p, int part, bool act,
-                                               ScoreFrag<D>& f, bool is_tail, bool opened,
-                                               const uint16_t* k_new, const float* qf, double* hb) {
-    constexpr int SV = ScoreFrag<D>::SV;
+                                               ScoreFrag<T, D>& f, bool is_tail, bool opened,
+                                               const T* k_new, const float* qf, double* hb) {
+    constexpr int SV = ScoreFrag<T, D>::SV, V = 16 / sizeof(T);
     const int G = L.G;
     if (act && is_tail) {
 #pragma unroll
         for (int i = 0; i < SV; ++i) {
-            const u32x4 x = ld4(k_new + part * (D / 8) + 8 * i);
+            const u32x4 x = ld4(k_new + part * (D / 8) + V * i);
             if (opened) {
                 f.kx[i] = x;
                 f.kn[i] = x;
+            } else if constexpr (sizeof(T) == 4) {
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    const float xv = __uint_as_float(x[h]);
+                    f.kx[i][h] = xv > __uint_as_float(f.kx[i][h]) ? x[h] : f.kx[i][h];
+                    f.kn[i][h] = xv < __uint_as_float(f.kn[i][h]) ? x[h] : f.kn[i][h];
+                }
             } else {
 #pragma unroll
                 for (int h = 0; h < 4; ++h) {
@@ -423,9 +430,9 @@ __device__ __forceinline__ double score_finish(const LayerView& L, int u, int p,
                     f.kn[i][h] = b;
                 }
             }
-            const size_t off = ((size_t)u * L.S + p) * D + part * (D / 8) + 8 * i;
-            st4((uint16_t*)L.kmax + off, f.kx[i]);
-            st4((uint16_t*)L.kmin + off, f.kn[i]);
+            const size_t off = ((size_t)u * L.S + p) * D + part * (D / 8) + V * i;
+            st4((T*)L.kmax + off, f.kx[i]);
+            st4((T*)L.kmin + off, f.kn[i]);
         }
     }
     const int c0 = part * (D / 8);
@@ -434,24 +441,40 @@ __device__ __forceinline__ double score_finish(const LayerView& L, int u, int p,
 #pragma unroll
     for (int i = 0; i < SV; ++i)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            kxf[8 * i + e] = bf2f(u16_at(f.kx[i], e));
-            knf[8 * i + e] = bf2f(u16_at(f.kn[i], e));
+        for (int e = 0; e < V; ++e) {
+            kxf[V * i + e] = vec_elem<T>(f.kx[i], e);
+            knf[V * i + e] = vec_elem<T>(f.kn[i], e);
         }
     double best = -INFINITY;
 #pragma unroll 1
     for (int j = 0; j < G; ++j) {
         const float* qj = qf + (size_t)j * qpad_row(D) + c0 + 4 * part;  // see qpad_index
-        double a0 = 0.0, a1 = 0.0;  // even and odd channels
+        double a;
+        if constexpr (sizeof(T) == 4) {
+            // products of two fp32 values are exact in fp64: the larger of the
+            // two is the one that q's sign picks, and each fused multiply-add
+            // rounds as the sum of the exact product
+            a = 0.0;
 #pragma unroll
-        for (int c = 0; c < D / 8; c += 4) {
-            const float4 qq = *reinterpret_cast<const float4*>(qj + c);
-            a0 += (double)fmaxf(qq.x * kxf[c], qq.x * knf[c]);
-            a1 += (double)fmaxf(qq.y * kxf[c + 1], qq.y * knf[c + 1]);
-            a0 += (double)fmaxf(qq.z * kxf[c + 2], qq.z * knf[c + 2]);
-            a1 += (double)fmaxf(qq.w * kxf[c + 3], qq.w * knf[c + 3]);
+            for (int c = 0; c < D / 8; c += 4) {
+                const float4 qq = *reinterpret_cast<const float4*>(qj + c);
+                a = fma((double)qq.x, (double)(qq.x >= 0.0f ? kxf[c] : knf[c]), a);
+                a = fma((double)qq.y, (double)(qq.y >= 0.0f ? kxf[c + 1] : knf[c + 1]), a);
+                a = fma((double)qq.z, (double)(qq.z >= 0.0f ? kxf[c + 2] : knf[c + 2]), a);
+                a = fma((double)qq.w, (double)(qq.w >= 0.0f ? kxf[c + 3] : knf[c + 3]), a);
+            }
+        } else {
+            double a0 = 0.0, a1 = 0.0;  // even and odd channels
+#pragma unroll
+            for (int c = 0; c < D / 8; c += 4) {
+                const float4 qq = *reinterpret_cast<const float4*>(qj + c);
+                a0 += (double)fmaxf(qq.x * kxf[c], qq.x * knf[c]);
+                a1 += (double)fmaxf(qq.y * kxf[c + 1], qq.y * knf[c + 1]);
+                a0 += (double)fmaxf(qq.z * kxf[c + 2], qq.z * knf[c + 2]);
+                a1 += (double)fmaxf(qq.w * kxf[c + 3], qq.w * knf[c + 3]);
+            }
+            a = a0 + a1;
         }
-        double a = a0 + a1;
         // the eight parts: pairs, then quads, then the two quads (the lanes of
         // a quad hold equal sums by then, so the mirror partner gives lane ^ 4's)
         a += dpp_f64<0xB1>(a);
@@ -862,8 +885,7 @@ __device__ __forceinline__ void count_ranked(bool mine, int* s_n) {
 }
 
 // Top-r refresh and eviction by a whole workgroup (every thread calls it; the
-// version of the rules in retention_wave for split units and for the fp32
-// epilogue kernel): with n ranked pages and k = floor(r*n), an evictable page is
+// version of the rules in retention_wave for split units): with n ranked pages and k = floor(r*n), an evictable page is
 // refreshed when at least n-k ranked pages score strictly less. meanwhile():
 // the caller's own work, done by the other wavefronts while wavefront 0
 // evicts. Slots below first hold no ranked page (the prompt region's, and
@@ -982,98 +1004,6 @@ __device__ __forceinline__ void retention_block(const LayerView& L, const UnitRe
         evict_wave(L, ur, s_state, s_ts, s_lid, out);
     }
     meanwhile();
-}
-
-// Top-r refresh by a whole workgroup (every thread calls it; the fused
-// fp32 kernel's version of the rule in retention_wave). With n ranked pages and
-// k = floor(r*n), an evictable page is refreshed when at least n-k ranked
-// pages score strictly less. Up to 256 slots this is counted directly.
-// Beyond, the workgroup finds theta, the (n-k)-th smallest ranked score, by
-// a radix select over order_key (eight 8-bit digits, most significant
-// first, a 256-bin histogram each) and refreshes the evictable pages
-// scoring above theta: the same pages, since fewer than n-k ranked scores
-// lie below theta and at least n-k lie at or below it. Slots below first
-// hold no ranked page (the prompt region's, when there is one). s_aux: 260
-// ints.
-__device__ void refresh_block(const LayerView& L, const UnitRec& ur, double r, const double* s_score,
-                              const int* s_state, int* s_ts, int* s_aux, int tid, int nthreads, int first) {
-    const int S = L.S, lane = tid & 63;
-    int* s_hist = s_aux;  // [256]
-    if (tid == 0) s_aux[256] = 0;
-    __syncthreads();
-    int cnt = 0;
-    for (int p = first + tid; p < S; p += nthreads) cnt += ranked(L, s_state[p]) ? 1 : 0;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) cnt += __shfl_xor(cnt, off);
-    if (lane == 0 && cnt) atomicAdd(&s_aux[256], cnt);
-    __syncthreads();
-    const int n = s_aux[256];
-    const int k = (int)floor(r * (double)n);
-    if (k == 0) return;
-    if (k == n) {  // every page refreshed
-        for (int p = first + tid; p < S; p += nthreads)
-            if (s_state[p] == kEvictable) s_ts[p] = ur.clock;
-        return;
-    }
-    if (S - first <= 256) {
-        for (int p = first + tid; p < S; p += nthreads) {
-            if (s_state[p] != kEvictable) continue;
-            const double sp = s_score[p];
-            int less = 0;
-#pragma unroll 8
-            for (int o = first; o < S; ++o) less += s_score[o] < sp;  // unranked slots hold +inf
-            if (less >= n - k) s_ts[p] = ur.clock;
-        }
-        return;
-    }
-    unsigned long long prefix = 0;
-    int want = n - k - 1;  // 0-based rank of theta among the ranked scores
-    for (int shift = 56; shift >= 0; shift -= 8) {
-        for (int b = tid; b < 256; b += nthreads) s_hist[b] = 0;
-        __syncthreads();
-        const unsigned long long high = shift == 56 ? 0ull : (~0ull << (shift + 8));
-        for (int p = first + tid; p < S; p += nthreads) {
-            if (!ranked(L, s_state[p])) continue;
-            const unsigned long long key = order_key(s_score[p]);
-            if ((key & high) == prefix) atomicAdd(&s_hist[(int)((key >> shift) & 255ull)], 1);
-        }
-        __syncthreads();
-        if (tid < 64) {  // wavefront 0 scans the bins: lane l holds bins 4l .. 4l+3
-            const int c0 = s_hist[4 * lane], c1 = s_hist[4 * lane + 1], c2 = s_hist[4 * lane + 2],
-                      c3 = s_hist[4 * lane + 3];
-            const int sum = c0 + c1 + c2 + c3;
-            int incl = sum;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int v = __shfl_up(incl, off);
-                if (lane >= off) incl += v;
-            }
-            const int excl = incl - sum;
-            if (excl <= want && want < incl) {
-                int w = want - excl, b = 4 * lane;
-                if (w >= c0) {
-                    w -= c0;
-                    ++b;
-                    if (w >= c1) {
-                        w -= c1;
-                        ++b;
-                        if (w >= c2) {
-                            w -= c2;
-                            ++b;
-                        }
-                    }
-                }
-                s_aux[257] = b;
-                s_aux[258] = w;
-            }
-        }
-        __syncthreads();
-        prefix |= (unsigned long long)s_aux[257] << shift;
-        want = s_aux[258];
-    }
-    const double theta = from_order_key(prefix);
-    for (int p = first + tid; p < S; p += nthreads)
-        if (s_state[p] == kEvictable && s_score[p] > theta) s_ts[p] = ur.clock;
 }
 
 // Writes the step's retention results to the pool and the optional outputs.
@@ -1295,15 +1225,15 @@ __device__ __forceinline__ void finish_units(const LayerView& L, const StepIO& i
 // columns = query heads), online softmax in base 2 with one cross-lane max,
 // PV as D/16 MFMAs of V^T times P^T. nv: valid rows among this lane's eight.
 template <int D>
-__device__ __forceinline__ void attend_block(const u32x4 (&kr)[2][D / 32], const u32x4 (&vr)[D / 16], int nv,
+__device__ __forceinline__ void attend_block(const u32x4 (&kr)[D / 16], const u32x4 (&vr)[D / 16], int nv,
                                              const bf16x8 (&qv)[D / 32], float scale_log2, float& m_run,
                                              float& l_run, f32x4 (&acc)[D / 16]) {
     constexpr int KS = D / 32, NB = D / 16;
     f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[0][ks]), qv[ks], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[1][ks]), qv[ks], s1, 0, 0, 0);
+        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[ks]), qv[ks], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[KS + ks]), qv[ks], s1, 0, 0, 0);
     }
     // x[j]: scaled logit of token 8*grp + j for head `col` (base 2)
     float x[8];
@@ -1338,8 +1268,103 @@ __device__ __forceinline__ void attend_block(const u32x4 (&kr)[2][D / 32], const
         acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vr[nb]), pb, acc[nb], 0, 0, 0);
 }
 
+// The same for fp32 pools, on 16 tokens: the products are fp32 and so are
+// their sums. A lane's 16-byte load of a key row holds channels 16j + 4grp ..
+// +3 of token `col`, whichever way the matrix cores then take it; the queries
+// come from LDS in the same order (s_q: this lane's head and channel group).
+// nv: valid rows among the four tokens whose probabilities this lane holds.
+//
+// G > 4 (v_mfma_f32_16x16x4_f32): element e is the left operand of step (j,
+// e), whose four channels are 16j + 4grp + e over the lane groups. The
+// probabilities leave that product as tokens 4grp + i of head `col`, which is
+// the right operand of the second one when its step tt takes the tokens 4grp +
+// tt: a lane loads values of those four rows, channels 64h + 4col .. +3, and
+// row i of the result's tile (h, e) is channel 64h + 16grp + 4i + e.
+//
+// G <= 4 (g4, v_mfma_f32_4x4x1_16b_f32, sixteen 4x4 products side by side): 16
+// columns would idle at a cost of 64 steps of 32 cycles per block, 6.8 us of
+// the 21.8 us that a step of 512 tokens took; 64 steps of 8 cycles do the
+// same. Block (grp, tg), tg = (lane >> 2) & 3, multiplies tokens 4tg .. +3
+// with the channels of its grp, head lane & 3; the four grp then add up, so
+// every one of them holds the same logits of tokens 4tg + i. In the second
+// product block (grp, tg) takes the tokens of its tg, channels 64h + 16grp +
+// 4i + e as row i, so the values are loaded at rows 4tg + tt, channels 64h +
+// 16grp + 4(lane & 3); the tg add up once, after the last block.
+template <int D, bool g4>
+__device__ __forceinline__ void attend_block_f32(const u32x4 (&kr)[D / 16], u32x4 (&vr)[D / 16], int nv,
+                                                 const float* s_q, int grp, float scale_log2, float& m_run,
+                                                 float& l_run, f32x4 (&acc)[D / 16]) {
+    constexpr int NS = g4 ? 4 : 2;  // sums side by side (the 4x4 products are short)
+    f32x4 s[NS];
+#pragma unroll
+    for (int e = 0; e < NS; ++e) s[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto logits = [&](auto mfma) {
+#pragma unroll
+        for (int j = 0; j < D / 16; ++j) {
+            const int c = 16 * j + 4 * grp;
+            const f32x4 q = *reinterpret_cast<const f32x4*>(s_q + c + 4 * (c / (D / 8)));  // see qpad_index
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e % NS] = mfma(__uint_as_float(kr[j][e]), q[e], s[e % NS]);
+        }
+    };
+    auto mfma4 = [](float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0); };
+    auto mfma16 = [](float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); };
+    if constexpr (g4) logits(mfma4);
+    else logits(mfma16);
+    float x[4], mb = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        x[v] = s[0][v] + s[1][v];
+        if constexpr (NS == 4) x[v] += s[2][v] + s[3][v];
+        if (g4) x[v] = sum_xor16_32(x[v]);
+        x[v] = (v < nv) ? x[v] * scale_log2 : -INFINITY;
+        mb = fmaxf(mb, x[v]);
+    }
+    if (g4) {
+        mb = fmaxf(mb, dpp_f32<0x124>(mb));
+        mb = fmaxf(mb, dpp_f32<0x128>(mb));
+    } else {
+        mb = max_xor16_32(mb);
+    }
+    const float m_new = fmaxf(m_run, mb);
+    if (__ballot(m_new > m_run) != 0ull) {
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        l_run *= alpha;
+#pragma unroll
+        for (int nb = 0; nb < D / 16; ++nb) acc[nb] *= alpha;
+        m_run = m_new;
+    }
+    float pj[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        pj[v] = __builtin_amdgcn_exp2f(x[v] - m_run);
+        l_run += pj[v];
+    }
+    if (__ballot(nv < 4) != 0ull) {  // rows that hold no token weigh 0 whatever is stored there
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt)
+#pragma unroll
+            for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) vr[tt * (D / 64) + h][e] = tt < nv ? vr[tt * (D / 64) + h][e] : 0u;
+    }
+    auto values = [&](auto mfma) {
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt)
+#pragma unroll
+            for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc[4 * h + e] = mfma(__uint_as_float(vr[tt * (D / 64) + h][e]), pj[tt], acc[4 * h + e]);
+    };
+    if constexpr (g4) values(mfma4);
+    else values(mfma16);
+}
+
 // ---------------------------------------------------------------------------
-// Step kernel, bf16 pools. One workgroup of NW wavefronts per (unit, split).
+// Step kernel. One workgroup of NW wavefronts per (unit, split). Described for
+// bf16 pools; fp32 pools run the same on blocks of 16 tokens, 16 KB either way
+// at head_dim 128.
 //
 // Attention (Algorithm 1, attention(Q, K_old::K_new, V_old::V_new)) over
 // every resident token, split-K over 32-token blocks. Each wavefront holds
@@ -1378,10 +1403,15 @@ __device__ __forceinline__ void attend_block(const u32x4 (&kr)[2][D / 32], const
 // The step of work item wi = unit * nsplit + split, by one workgroup (the
 // arguments by value: as kernel arguments, they leave the registers of the
 // block loop alone).
-template <int D, int NW, bool AGG, int LM, bool NT, bool SPLIT>
+template <typename T, int D, int NW, bool AGG, int LM, bool NT, bool SPLIT, bool G4>
 __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_log2, double r, const int wi) {
     constexpr bool fused = !SPLIT;
-    constexpr int KS = D / 32, NB = D / 16, BLK = 32 * D;
+    constexpr bool F32 = sizeof(T) == 4;
+    constexpr int KS = D / 32, NB = D / 16;  // 16-byte vectors per lane: NB of a block's keys and of its values
+    constexpr int BT = F32 ? 16 : 32, BLK = BT * D;  // tokens and elements of a block
+    constexpr int BPB = 32 / BT;                     // blocks in the 32 tokens that the plan and the lists count in
+    constexpr int TPL = BT / 4;                      // tokens whose probabilities a lane holds
+    constexpr int VE = 16 / sizeof(T);               // elements of a 16-byte vector
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ float s_m[NW][16];
     __shared__ float s_l[NW][16];
@@ -1390,8 +1420,8 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
     __shared__ int s_nsel;  // LM 2: prompt blocks chosen
     __shared__ int s_lo;    // LM 2: the topk-th largest lower end of a prompt bound (ordered bits)
     __shared__ int s_ncand; // LM 2: candidate prompt pages
-    __shared__ __align__(16) uint16_t s_kn[D];  // the new token's key and value, staged so that
-    __shared__ __align__(16) uint16_t s_vn[D];  // no read in the block loop waits on memory
+    __shared__ __align__(16) T s_kn[D];  // the new token's key and value, staged so that
+    __shared__ __align__(16) T s_vn[D];  // no read in the block loop waits on memory
 
     const int G = L.G, S = L.S, ps = L.ps;
     float* s_qf = reinterpret_cast<float*>(smem);  // [G][D+32] q in fp32, padded: qpad_index
@@ -1416,6 +1446,10 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int grp = lane >> 4, col = lane & 15;
+    // tg: which of the block's TPL-token runs this lane's probabilities are of
+    constexpr bool g4 = G4;
+    const int tg = g4 ? (lane >> 2) & 3 : grp;
+    const int vcol = g4 ? 16 * grp + 4 * (lane & 3) : 4 * col;  // fp32: channel of a value load
     const int nsplit = L.nsplit;
     const unsigned uwi = (unsigned)wi;  // (unsigned arithmetic, as on blockIdx.x)
     const int u = uwi / nsplit, split = uwi - (uwi / nsplit) * nsplit;
@@ -1441,35 +1475,44 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
         for (int i = tid; i < hi - lo; i += NW * 64) s_list[i] = L.blist[(size_t)u * L.lcap_blk + lo + i];
         __syncthreads();
     } else {
-        lo = split * L.bps;
-        hi = max(lo, min(L.nblk, lo + L.bps));
-        sb0 = lo;
-        sb1 = hi;
+        sb0 = split * L.bps;
+        sb1 = max(sb0, min(L.nblk, sb0 + L.bps));
+        lo = sb0 * BPB;
+        hi = sb1 * BPB;
     }
-    const int nown = hi - lo;                  // claims of this workgroup
+    const int nown = LM ? (hi - lo) * BPB : hi - lo;  // claims of this workgroup
     const int bend = LM ? 0x40000000 : hi;     // no block: every block index lies below
     auto real = [&](int x) { return x < bend; };
-    const uint16_t* qg = (const uint16_t*)io.q + (size_t)u * G * D;
-    const uint16_t* kn_g = (const uint16_t*)io.k_new + (size_t)u * D;
-    const uint16_t* vn_g = (const uint16_t*)io.v_new + (size_t)u * D;
-    const uint16_t* Ku = (const uint16_t*)L.K + (size_t)u * L.Lcap * D;
-    const uint16_t* Vu = (const uint16_t*)L.V + (size_t)u * L.Lcap * D;
+    const T* qg = (const T*)io.q + (size_t)u * G * D;
+    const T* kn_g = (const T*)io.k_new + (size_t)u * D;
+    const T* vn_g = (const T*)io.v_new + (size_t)u * D;
+    const T* Ku = (const T*)L.K + (size_t)u * L.Lcap * D;
+    const T* Vu = (const T*)L.V + (size_t)u * L.Lcap * D;
     // fills the attention sees (the plain fill pointer where they are the
     // same: read through it, the first block's fill arrives sooner)
     const int32_t* fu = (LM == 1 ? L.fill_att : L.fill) + base;
-    auto ldb = [&](const uint16_t* p) {
+    auto ldb = [&](const T* p) {
         if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
         else return ld4(p);
     };
-    auto load_block = [&](int b, u32x4 (&kr)[2][KS], u32x4 (&vr)[NB]) {
-        const uint16_t* Kb = Ku + (size_t)b * BLK + lane * 8;
-        const uint16_t* Vb = Vu + (size_t)b * BLK + lane * 8;
+    auto load_block = [&](int b, u32x4 (&kr)[NB], u32x4 (&vr)[NB]) {
+        if constexpr (F32) {
+            const T* Kb = Ku + (size_t)b * BLK + col * D + 4 * grp;
+            const T* Vb = Vu + (size_t)b * BLK + 4 * tg * D + vcol;
 #pragma unroll
-        for (int qq = 0; qq < 2; ++qq)
+            for (int j = 0; j < NB; ++j) kr[j] = ldb(Kb + 16 * j);
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) kr[qq][ks] = ldb(Kb + (qq * KS + ks) * 512);
+            for (int tt = 0; tt < 4; ++tt)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) vr[nb] = ldb(Vb + nb * 512);
+                for (int h = 0; h < D / 64; ++h) vr[tt * (D / 64) + h] = ldb(Vb + tt * D + 64 * h);
+        } else {
+            const T* Kb = Ku + (size_t)b * BLK + lane * 8;
+            const T* Vb = Vu + (size_t)b * BLK + lane * 8;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) kr[i] = ldb(Kb + i * 512);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) vr[nb] = ldb(Vb + nb * 512);
+        }
     };
 
     // Loads complete in issue order, so the small reads go out first: the
@@ -1483,18 +1526,18 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
     // claim index i of the own blocks, ascending or (L.rev) descending
     auto blk_of = [&](int i) {
         const int j = L.rev ? nown - 1 - i : i;
-        if constexpr (LM == 1) return s_list[j];
+        if constexpr (LM == 1) return s_list[j / BPB] * BPB + j % BPB;
         else if constexpr (LM == 2) return nbp + j;
         else return lo + j;
     };
     int b = (w < nown) ? blk_of(w) : bend;  // (LM 2: a prompt block, once they are chosen)
-    const int slot_first = (32 * b + 8 * grp) / ps;
+    const int slot_first = (BT * b + TPL * tg) / ps;
     const int fill_first = (real(b) && slot_first < S) ? fu[slot_first] : 0;
     // unconditional (clamped) reads: a read under a branch draws its first
     // use into the branch, with a wait for it ahead of the block loads
-    const uint16_t q_first = qg[tid < G * D ? tid : 0];
-    const int t_new = tid < D / 8 ? tid : 0;
-    const u32x4 kn_first = ld4(kn_g + 8 * t_new), vn_first = ld4(vn_g + 8 * t_new);
+    const T q_first = qg[tid < G * D ? tid : 0];
+    const int t_new = tid < D / VE ? tid : 0;
+    const u32x4 kn_first = ld4(kn_g + VE * t_new), vn_first = ld4(vn_g + VE * t_new);
     const int s_first = tid < S ? tid : 0;
     const int st_first = L.state[base + s_first], ts_first = L.ts[base + s_first], lid_first = L.lid[base + s_first];
     const int pf_first = LM == 2 ? fu[tid < L.dbase ? tid : 0] : 0;  // LM 2: a prompt page's fill
@@ -1507,13 +1550,15 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
         lid_sec = L.lid[base + sl_sec];
         pf_sec = fu[pg_sec];
     }
-    bf16x8 qv[KS];
+    bf16x8 qv[F32 ? 1 : KS];  // bf16: the queries as MFMA operands (fp32 reads them from LDS)
+    if constexpr (!F32) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        const u32x4 x = (col < G) ? ld4(qg + (size_t)col * D + 32 * ks + 8 * grp) : u32x4{0u, 0u, 0u, 0u};
-        qv[ks] = __builtin_bit_cast(bf16x8, x);
+        for (int ks = 0; ks < KS; ++ks) {
+            const u32x4 x = (col < G) ? ld4(qg + (size_t)col * D + 32 * ks + 8 * grp) : u32x4{0u, 0u, 0u, 0u};
+            qv[ks] = __builtin_bit_cast(bf16x8, x);
+        }
     }
-    u32x4 kr_next[2][KS], vr_next[NB];
+    u32x4 kr_next[NB], vr_next[NB];
     int f_first = 0;  // LM 2: the first block's fill
     if constexpr (LM == 2) {
         // The staging first (the other instances stage below, behind the first
@@ -1570,7 +1615,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
 
     const int ns = ur.ns, nf = ur.nf;
     const bool opened = ur.opened();
-    const int row_new = ns * ps + nf, b_new = row_new >> 5, tt_new = row_new & 31;
+    const int row_new = ns * ps + nf, b_new = row_new / BT, tt_new = row_new % BT;
     bool decided = false;  // this wavefront has passed the score barrier
     // the block of claim index i, or bend when none is left (LM 2: the decode
     // blocks, then the chosen prompt blocks)
@@ -1587,27 +1632,27 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
     const int sl0 = max(L.rank_pinned ? 0 : pinned, min(S, (32 * sb0 + ps - 1) / ps));
     const int sl1 = min(S, (32 * sb1 + ps - 1) / ps);
 
-    // fill of the page holding this lane's 8 rows of block b (page_size % 8 == 0)
+    // fill of the page holding this lane's TPL rows of block b (page_size % 8 == 0)
     auto row_fill = [&](int b) {
-        const int slot = (32 * b + 8 * grp) / ps;
+        const int slot = (BT * b + TPL * tg) / ps;
         if constexpr (LM == 2)
             if (slot < L.dbase) return s_fatt[slot];  // read only once the prompt pages are chosen
         return (slot < S) ? (slot == ns ? nf + 1 : fu[slot]) : 0;
     };
     auto valid_rows = [&](int b, int f) {
-        const int t0 = 32 * b + 8 * grp;
-        return min(max(f - (t0 - (t0 / ps) * ps), 0), 8);
+        const int t0 = BT * b + TPL * tg;
+        return min(max(f - (t0 - (t0 / ps) * ps), 0), TPL);
     };
     int f_next = f_first;
     if constexpr (LM != 2) {
         if (real(b)) f_next = (w < nown) ? (slot_first < S ? (slot_first == ns ? nf + 1 : fill_first) : 0) : row_fill(b);
 
         // staging for the scores and the epilogue
-        if (tid < G * D) s_qf[qpad_index<D>(tid)] = bf2f(q_first);
-        for (int i = tid + NW * 64; i < G * D; i += NW * 64) s_qf[qpad_index<D>(i)] = bf2f(qg[i]);
-        if (tid < D / 8) {
-            st4(&s_kn[8 * tid], kn_first);
-            st4(&s_vn[8 * tid], vn_first);
+        if (tid < G * D) s_qf[qpad_index<D>(tid)] = to_f(q_first);
+        for (int i = tid + NW * 64; i < G * D; i += NW * 64) s_qf[qpad_index<D>(i)] = to_f(qg[i]);
+        if (tid < D / VE) {
+            st4(&s_kn[VE * tid], kn_first);
+            st4(&s_vn[VE * tid], vn_first);
         }
         if (fused) {
             if (tid < S) stage_slot(ur, tid, st_first, ts_first, lid_first, s_score, s_state, s_ts, s_lid);
@@ -1663,9 +1708,9 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
                     const int c = c0 + (lane >> 3);
                     const bool act = c < nc;
                     const int p = act ? s_cand[c] : 0;
-                    ScoreFrag<D> f;
-                    score_issue<D>(L, u, p, lane & 7, act, f);
-                    const double sc = score_finish<D>(L, u, p, lane & 7, act, f, false, false, s_kn, s_qf, nullptr);
+                    ScoreFrag<T, D> f;
+                    score_issue<T, D>(L, u, p, lane & 7, act, f);
+                    const double sc = score_finish<T, D>(L, u, p, lane & 7, act, f, false, false, s_kn, s_qf, nullptr);
                     if (act && (lane & 7) == 0) s_ex[c] = sc;
                 }
                 lds_barrier();
@@ -1721,12 +1766,12 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
     const int npass = (sl1 - sl0 - 8 * w > 0) ? (sl1 - sl0 - 8 * w + 8 * NW - 1) / (8 * NW) : 0;
     const int npass_all = (sl1 - sl0 + 8 * NW - 1) / (8 * NW);  // passes of wavefront 0, the most
     int pass = 0;
-    ScoreFrag<D> frag;
+    ScoreFrag<T, D> frag;
     bool act_cur = false;
     auto score_step = [&]() {
         const int p = pass_page(pass);
         double* hb = (AGG && act_cur) ? (fused ? s_hb : L.score + base * G) + (size_t)p * G : nullptr;
-        const double sc = score_finish<D>(L, u, p, part, act_cur, frag, p == ns, opened, s_kn, s_qf, hb);
+        const double sc = score_finish<T, D>(L, u, p, part, act_cur, frag, p == ns, opened, s_kn, s_qf, hb);
         if (act_cur && part == 0 && !AGG) {
             if (fused) s_score[p] = sc;
             else publish(L.score + base + p, sc);
@@ -1735,7 +1780,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
         if (pass < npass) {
             const int pn = pass_page(pass);
             act_cur = pass_act(pn);
-            score_issue<D>(L, u, pn, part, act_cur && !(pn == ns && opened), frag);
+            score_issue<T, D>(L, u, pn, part, act_cur && !(pn == ns && opened), frag);
         }
     };
     // retention policy once every wavefront's scores are in LDS
@@ -1756,7 +1801,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
         if (npass > 0) {
             const int p = pass_page(0);
             act_cur = pass_act(p);
-            score_issue<D>(L, u, p, part, act_cur && !(p == ns && opened), frag);
+            score_issue<T, D>(L, u, p, part, act_cur && !(p == ns && opened), frag);
         }
     };
     // the first score pass's loads go out now, behind the first blocks' (L.early),
@@ -1766,11 +1811,9 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
     int it = 0;
     while (b < bend) {
         const int f_cur = f_next;
-        u32x4 kr[2][KS], vr[NB];
+        u32x4 kr[NB], vr[NB];
 #pragma unroll
-        for (int qq = 0; qq < 2; ++qq)
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) kr[qq][ks] = kr_next[qq][ks];
+        for (int i = 0; i < NB; ++i) kr[i] = kr_next[i];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) vr[nb] = vr_next[nb];
         // one claim per wavefront: from the LDS counter, or (L.det) a fixed
@@ -1785,36 +1828,62 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
         const int nv = valid_rows(b, f_cur);
         if (__ballot(nv > 0) != 0ull) {
             if (b == b_new) {  // the new token: K/V from the inputs
-                const int i_new = 4 * (tt_new >> 3) + (tt_new & 3), q_new = (tt_new >> 2) & 1;
-                if (col == i_new) {
+                if constexpr (F32) {
+                    if (col == tt_new) {
 #pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) {
-                        const u32x4 x = ld4(&s_kn[32 * ks + 8 * grp]);
-                        if (q_new == 0) kr[0][ks] = x; else kr[1][ks] = x;
+                        for (int j = 0; j < NB; ++j) kr[j] = ld4(&s_kn[16 * j + 4 * grp]);
                     }
-                }
-                if (grp == (tt_new >> 3)) {
-                    const int j_new = tt_new & 7;
+                    if (tg == (tt_new >> 2)) {
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) {
-                        const uint32_t val = s_vn[16 * nb + col];
+                        for (int tt = 0; tt < 4; ++tt)
+                            if (tt == (tt_new & 3)) {
 #pragma unroll
-                        for (int h = 0; h < 4; ++h) {
-                            if ((j_new >> 1) == h) {
-                                const int sh = (j_new & 1) * 16;
-                                vr[nb][h] = (vr[nb][h] & ~(0xFFFFu << sh)) | (val << sh);
+                                for (int h = 0; h < D / 64; ++h) vr[tt * (D / 64) + h] = ld4(&s_vn[64 * h + vcol]);
+                            }
+                    }
+                    // append: the new token joins the pool (Algorithm 1, decode-stage store)
+                    T* Kw = (T*)L.K + ((size_t)u * L.Lcap + row_new) * D;
+                    T* Vw = (T*)L.V + ((size_t)u * L.Lcap + row_new) * D;
+                    if (lane < D / 4) {
+                        st4(Kw + 4 * lane, ld4(&s_kn[4 * lane]));
+                        st4(Vw + 4 * lane, ld4(&s_vn[4 * lane]));
+                    }
+                } else {
+                    const int i_new = 4 * (tt_new >> 3) + (tt_new & 3), q_new = (tt_new >> 2) & 1;
+                    if (col == i_new) {
+#pragma unroll
+                        for (int ks = 0; ks < KS; ++ks) {
+                            const u32x4 x = ld4(&s_kn[32 * ks + 8 * grp]);
+                            if (q_new == 0) kr[ks] = x; else kr[KS + ks] = x;
+                        }
+                    }
+                    if (grp == (tt_new >> 3)) {
+                        const int j_new = tt_new & 7;
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb) {
+                            const uint32_t val = s_vn[16 * nb + col];
+#pragma unroll
+                            for (int h = 0; h < 4; ++h) {
+                                if ((j_new >> 1) == h) {
+                                    const int sh = (j_new & 1) * 16;
+                                    vr[nb][h] = (vr[nb][h] & ~(0xFFFFu << sh)) | (val << sh);
+                                }
                             }
                         }
                     }
+                    // append: the new token joins the pool (Algorithm 1, decode-stage store)
+                    T* Kw = (T*)L.K + (size_t)u * L.Lcap * D;
+                    T* Vw = (T*)L.V + (size_t)u * L.Lcap * D;
+                    if (lane < D / 8) st4(Kw + k_off<D>(row_new, lane * 8), ld4(&s_kn[lane * 8]));
+                    for (int c = lane; c < D; c += 64) Vw[v_off<D>(row_new, c)] = s_vn[c];
                 }
-                // append: the new token joins the pool (Algorithm 1, decode-stage store)
-                uint16_t* Kw = (uint16_t*)L.K + (size_t)u * L.Lcap * D;
-                uint16_t* Vw = (uint16_t*)L.V + (size_t)u * L.Lcap * D;
-                if (lane < D / 8) st4(Kw + k_off<D>(row_new, lane * 8), ld4(&s_kn[lane * 8]));
-                for (int c = lane; c < D; c += 64) Vw[v_off<D>(row_new, c)] = s_vn[c];
             }
 
-            attend_block<D>(kr, vr, nv, qv, scale_log2, m_run, l_run, acc);
+            if constexpr (F32)
+                attend_block_f32<D, g4>(kr, vr, nv, s_qf + min(g4 ? lane & 3 : col, G - 1) * qpad_row(D), grp, scale_log2, m_run, l_run,
+                                    acc);
+            else
+                attend_block<D>(kr, vr, nv, qv, scale_log2, m_run, l_run, acc);
         }
         // this block's registers are free again
         if (it == 0 && !early) {
@@ -1834,16 +1903,35 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
     if (!decided) scores_done();
 
     // park this wavefront's partial attention in LDS
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
-    if (grp == 0) {
-        s_m[w][col] = m_run;
-        s_l[w][col] = l_run;
+    const int head = g4 ? lane & 3 : col;
+    if (g4) {
+        l_run = sum_ror4_8(l_run);
+    } else {
+        l_run += __shfl_xor(l_run, 16);
+        l_run += __shfl_xor(l_run, 32);
     }
-    if (col < G) {
+    if (g4 ? lane < 4 : grp == 0) {
+        s_m[w][head] = m_run;
+        s_l[w][head] = l_run;
+    }
+    float* o = &s_o[((size_t)w * G + head) * (D + 4)];
+    if constexpr (F32) {  // tile (h, e), row i: channel 64h + 16grp + 4i + e
+        if (g4) {
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-            *reinterpret_cast<f32x4*>(&s_o[((size_t)w * G + col) * (D + 4) + 16 * nb + 4 * grp]) = acc[nb];
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[nb][i] = sum_ror4_8(acc[nb][i]);
+        }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int h = nb >> 2, i = nb & 3;
+            if (head < G && (!g4 || tg == i))
+                *reinterpret_cast<f32x4*>(o + 64 * h + 16 * grp + 4 * i) =
+                    f32x4{acc[4 * h][i], acc[4 * h + 1][i], acc[4 * h + 2][i], acc[4 * h + 3][i]};
+        }
+    } else if (col < G) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<f32x4*>(o + 16 * nb + 4 * grp) = acc[nb];
     }
     lds_barrier();  // partials parked, retention decided
     // the state goes out first (every block has been read), its stores
@@ -1865,7 +1953,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
             Ls += wt * s_l[ww][h];
         }
         if (nsplit == 1) {  // the whole unit: the output itself
-            ((uint16_t*)io.out)[((size_t)u * G + h) * D + c] = f2bf(O / Ls);
+            ((T*)io.out)[((size_t)u * G + h) * D + c] = from_f<T>(O / Ls);
         } else {
             float* pp = L.part + (((size_t)u * nsplit + split) * G + h) * (D + 2);
             publish(pp + c, O);
@@ -1886,10 +1974,10 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
             const MergeFirst mf = merge_first(L, u, tid);
             merge_stage(L, u, mf, reinterpret_cast<float*>(smem), tid, NW * 64);
             __syncthreads();
-            merge_out<uint16_t>(L, io, u, mf, reinterpret_cast<float*>(smem), tid, NW * 64);
+            merge_out<T>(L, io, u, mf, reinterpret_cast<float*>(smem), tid, NW * 64);
         }
         if (nu > 1 && !arrive_last(L.arrived + L.U + u / nu, nu, &s_last)) return;
-        finish_units<uint16_t>(L, io, r, u / nu * nu, nu, nu == 1 && nsplit > 1, smem, s_aux, ret, tid, NW * 64);
+        finish_units<T>(L, io, r, u / nu * nu, nu, nu == 1 && nsplit > 1, smem, s_aux, ret, tid, NW * 64);
     }
 }
 
@@ -1897,332 +1985,14 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
 template <int D, int NW, bool AGG, int LM, bool NT, bool SPLIT>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_bf16(
     LayerView L, StepIO io, float scale_log2, double r) {
-    step_item<D, NW, AGG, LM, NT, SPLIT>(L, io, scale_log2, r, blockIdx.x);
+    step_item<uint16_t, D, NW, AGG, LM, NT, SPLIT, false>(L, io, scale_log2, r, blockIdx.x);
 }
 
-// fp32 pools: the step of one split of a unit's rows by one wavefront, over
-// its rows in chunks of 64 tokens. In a chunk each lane takes one token: its
-// row of K is loaded whole (the loads go out with the unit record's, before
-// the fills say which rows hold tokens) and dotted with the G queries from
-// LDS. The online softmax then updates each head across the wavefront (base
-// 2), and the value pass turns to lanes across channels, one token at a
-// time. Rows are loaded whether or not they hold a token, so that no load
-// waits for the fills; a row holding none enters the sums as zeros with
-// weight 0. Page scores: eight lanes per page, each over D/8 channels, fp32
-// products formed exactly in fp64 and added there, then summed over the
-// eight lanes (a butterfly, so every lane of a page holds the same sum);
-// each pass's loads go out one pass ahead, the first at entry.
-// s_q: the unit's queries [GM][D] in LDS (heads past G zero), staged by the
-// caller; s_p: this wavefront's [GM][64] weights in LDS; partial: the split's
-// partial [G][D+2] (output, max, sum); score: the unit's [S] page scores, or
-// [S][G] per-head bounds with the softmax aggregation.
-template <int D, int GM>
-__device__ __forceinline__ void f32_split(const LayerView& L, const StepIO& io, float scale_log2, int u, int split,
-                                          const float* s_q, const float* s_kn, const float* s_vn, float (*s_p)[64],
-                                          float* partial, double* score) {
-    constexpr int DPL = D / 64;  // channels per lane in the value pass
-    constexpr int CPP = D / 8;   // channels per lane in the page scores
-    constexpr int VG = GM * DPL >= 32 ? 8 : 16;  // tokens whose value rows load together
-    const int lane = threadIdx.x & 63;
-    const int G = L.G, S = L.S, ps = L.ps;
-    const size_t base = (size_t)u * S;
-    const int t0 = split * L.bps * 32;
-    const int t1 = max(t0, min(min(S * ps, 32 * L.nblk), t0 + L.bps * 32));
-    const float* Ku = (const float*)L.K + (size_t)u * L.Lcap * D;
-    const float* Vu = (const float*)L.V + (size_t)u * L.Lcap * D;
-    const int32_t* fu = L.fill_att + base;  // fills the attention sees
-    // the small reads first (loads complete in issue order): the unit record
-    // and the first chunk's fills, then the key and value rows
-    const int32_t* U4 = L.unit + (size_t)u * kUnitFields;
-    const int ns = U4[kNextSlot], nf = U4[kNextFill];
-    int f_pre = fu[min(t0 + lane, max(t1 - 1, 0)) / ps];
-
-    // this lane's key row; the first chunk's now (rows below t1 lie inside
-    // the unit's pool)
-    float kr[D];
-    auto load_key = [&](const float* kp) {
-#pragma unroll
-        for (int c = 0; c < D; c += 4) {
-            const float4 x = *reinterpret_cast<const float4*>(kp + c);
-            kr[c] = x.x;
-            kr[c + 1] = x.y;
-            kr[c + 2] = x.z;
-            kr[c + 3] = x.w;
-        }
-    };
-    load_key(Ku + (size_t)min(t0 + lane, max(t1 - 1, 0)) * D);
-    // VPRE (head_dim 64, up to 8 head slots, where the registers allow): the
-    // chunk's 64 value rows (one channel per lane) load together with its key
-    // rows, before the fills and the unit record arrive, and the new token's
-    // value is substituted afterwards
-    constexpr bool VPRE = D == 64 && GM <= 8;
-    float vpre[VPRE ? 64 : 1];
-    auto load_vals = [&](int c0) {
-        if constexpr (VPRE) {
-#pragma unroll
-            for (int e = 0; e < 64; ++e) vpre[e] = Vu[(size_t)min(c0 + e, max(t1 - 1, 0)) * D + lane];
-        }
-    };
-    load_vals(t0);
-    const float vn_lane = VPRE ? s_vn[lane] : 0.0f;
-    // page state and representative keys of a score pass (pages pb .. pb+7,
-    // clamped into the split's pages), loaded one pass ahead
-    const int sl0 = min(S, (t0 + ps - 1) / ps), sl1 = min(S, (t1 + ps - 1) / ps);
-    const int part = lane & 7, cb = part * CPP;
-    float4 kx_nx[CPP / 4], kn_nx[CPP / 4];
-    int st_nx = kFree;
-    auto score_load = [&](int pb) {
-        const size_t p = base + min(pb + (lane >> 3), sl1 - 1);
-        st_nx = L.state[p];
-#pragma unroll
-        for (int c = 0; c < CPP; c += 4) {
-            kx_nx[c / 4] = *reinterpret_cast<const float4*>((const float*)L.kmax + p * D + cb + c);
-            kn_nx[c / 4] = *reinterpret_cast<const float4*>((const float*)L.kmin + p * D + cb + c);
-        }
-    };
-    if (sl0 < sl1) score_load(sl0);
-    const bool opened = nf == 0;
-    const int row_new = ns * ps + nf;
-
-    float m[GM], l[GM], acc[GM][DPL];
-#pragma unroll
-    for (int j = 0; j < GM; ++j) {
-        m[j] = -INFINITY;
-        l[j] = 0.0f;
-#pragma unroll
-        for (int i = 0; i < DPL; ++i) acc[j][i] = 0.0f;
-    }
-    for (int c0 = t0; c0 < t1; c0 += 64) {
-        const int t = c0 + lane;
-        if (c0 > t0) {  // later chunks' fills, key (and value) rows
-            f_pre = fu[min(t, t1 - 1) / ps];
-            load_key(Ku + (size_t)min(t, t1 - 1) * D);
-            load_vals(c0);
-        }
-        bool valid = false;
-        if (t < t1) {
-            const int slot = t / ps;
-            const int f = (slot == ns) ? nf + 1 : f_pre;
-            valid = t - slot * ps < f;
-        }
-        const unsigned long long vmask = __ballot(valid);
-        if (vmask == 0) continue;
-        if (t == row_new) load_key(s_kn);
-        // the heads' sums side by side (each in channel order)
-        float sc[GM];
-#pragma unroll
-        for (int j = 0; j < GM; ++j) sc[j] = 0.0f;
-#pragma unroll
-        for (int c = 0; c < D; c += 4) {
-#pragma unroll
-            for (int j = 0; j < GM; ++j) {
-                const float4 q4 = *reinterpret_cast<const float4*>(s_q + j * D + c);
-                sc[j] = fmaf(q4.x, kr[c], sc[j]);
-                sc[j] = fmaf(q4.y, kr[c + 1], sc[j]);
-                sc[j] = fmaf(q4.z, kr[c + 2], sc[j]);
-                sc[j] = fmaf(q4.w, kr[c + 3], sc[j]);
-            }
-        }
-        // every head slot runs (those past G on zero queries, never written out)
-#pragma unroll
-        for (int j = 0; j < GM; ++j) {
-            const float x = valid ? sc[j] * scale_log2 : -INFINITY;
-            const float mx = wave_max_dpp(x);
-            const float m_new = fmaxf(m[j], mx);  // finite: some lane holds a token
-            const float alpha = __builtin_amdgcn_exp2f(m[j] - m_new);
-            const float p = valid ? __builtin_amdgcn_exp2f(x - m_new) : 0.0f;
-            l[j] = l[j] * alpha + wave_sum_dpp(p);
-#pragma unroll
-            for (int i = 0; i < DPL; ++i) acc[j][i] *= alpha;
-            s_p[j][lane] = p;
-            m[j] = m_new;
-        }
-        wave_lds_sync();
-        if constexpr (VPRE) {
-#pragma unroll
-            for (int e = 0; e < 64; ++e) {
-                const uint32_t keep = 0u - (uint32_t)((vmask >> e) & 1ull);  // all ones or zero
-                const float v = __uint_as_float(__float_as_uint(c0 + e == row_new ? vn_lane : vpre[e]) & keep);
-#pragma unroll
-                for (int j = 0; j < GM; ++j) acc[j][0] = fmaf(s_p[j][e], v, acc[j][0]);
-            }
-        } else {
-#pragma unroll
-        for (int g0 = 0; g0 < 64; g0 += VG) {
-            float vr[VG][DPL];
-#pragma unroll
-            for (int e = 0; e < VG; ++e) {
-                const int tt = c0 + g0 + e;
-                const uint32_t keep = 0u - (uint32_t)((vmask >> (g0 + e)) & 1ull);  // all ones or zero
-                const float* vp = Vu + (size_t)min(tt, t1 - 1) * D;
-#pragma unroll
-                for (int i = 0; i < DPL; ++i) {
-                    const float x = tt == row_new ? s_vn[lane + 64 * i] : vp[lane + 64 * i];
-                    vr[e][i] = __uint_as_float(__float_as_uint(x) & keep);
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < VG; ++e)
-#pragma unroll
-                for (int j = 0; j < GM; ++j) {
-                    const float p = s_p[j][g0 + e];
-#pragma unroll
-                    for (int i = 0; i < DPL; ++i) acc[j][i] = fmaf(p, vr[e][i], acc[j][i]);
-                }
-        }
-        }
-        wave_lds_sync();  // the weights are read before the next chunk writes them
-    }
-#pragma unroll
-    for (int j = 0; j < GM; ++j) {
-        if (j >= G) break;
-        float* pp = partial + (size_t)j * (D + 2);
-#pragma unroll
-        for (int i = 0; i < DPL; ++i) pp[lane + 64 * i] = acc[j][i];
-        if (lane == 0) {
-            pp[D] = m[j];
-            pp[D + 1] = l[j];
-        }
-    }
-    if (row_new >= t0 && row_new < t1) {  // append
-        float* Kw = (float*)L.K + ((size_t)u * L.Lcap + row_new) * D;
-        float* Vw = (float*)L.V + ((size_t)u * L.Lcap + row_new) * D;
-        for (int c = lane; c < D; c += 64) {
-            Kw[c] = s_kn[c];
-            Vw[c] = s_vn[c];
-        }
-    }
-    // page scores: pages whose first row lies in this split, eight at a time
-    for (int pb = sl0; pb < sl1; pb += 8) {
-        const int p = pb + (lane >> 3);
-        const bool tail = p == ns;
-        const bool act = p < sl1 && (tail || ranked(L, st_nx));
-        float hi[CPP], lo[CPP];
-#pragma unroll
-        for (int c = 0; c < CPP; c += 4) {
-            const float4 a = kx_nx[c / 4], b = kn_nx[c / 4];
-            hi[c] = act ? a.x : 0.f, hi[c + 1] = act ? a.y : 0.f, hi[c + 2] = act ? a.z : 0.f;
-            hi[c + 3] = act ? a.w : 0.f;
-            lo[c] = act ? b.x : 0.f, lo[c + 1] = act ? b.y : 0.f, lo[c + 2] = act ? b.z : 0.f;
-            lo[c + 3] = act ? b.w : 0.f;
-        }
-        if (pb + 8 < sl1) score_load(pb + 8);
-        float* kx = (float*)L.kmax + (base + p) * D + cb;
-        float* kn = (float*)L.kmin + (base + p) * D + cb;
-        if (act && tail) {
-#pragma unroll
-            for (int c = 0; c < CPP; ++c) {
-                const float x = s_kn[cb + c];
-                hi[c] = opened ? x : fmaxf(hi[c], x);
-                lo[c] = opened ? x : fminf(lo[c], x);
-                kx[c] = hi[c];
-                kn[c] = lo[c];
-            }
-        }
-        double best = -INFINITY;
-#pragma unroll 1
-        for (int j = 0; j < G; ++j) {
-            double a = 0.0;
-#pragma unroll
-            for (int c = 0; c < CPP; ++c) {
-                const double qd = (double)s_q[j * D + cb + c];
-                const double x = qd * (double)hi[c], y = qd * (double)lo[c];
-                a += x > y ? x : y;
-            }
-            a += __shfl_xor(a, 1);
-            a += __shfl_xor(a, 2);
-            a += __shfl_xor(a, 4);
-            best = a > best ? a : best;
-            if (act && L.agg && part == 0) score[(size_t)p * G + j] = a;
-        }
-        if (act && !L.agg && part == 0) score[p] = best;
-    }
-}
-
-// Step kernel, fp32 pools, split plan: one wavefront per (unit, split); the
-// epilogue kernel merges the splits and runs the retention.
-template <int D, int GM>
-__global__ __launch_bounds__(64) void k_step_f32(LayerView L, StepIO io, float scale_log2) {
-    __shared__ __align__(16) float s_q[GM * D];
-    __shared__ __align__(16) float s_kn[D], s_vn[D];  // the new token's key and value
-    __shared__ float s_p[GM][64];  // the chunk's weights, per head and token
-    const int nsplit = L.nsplit;
-    const int u = blockIdx.x / nsplit, split = blockIdx.x - (blockIdx.x / nsplit) * nsplit;
-    if (io.active != nullptr && io.active[u / L.nkv] == 0) return;
-    const int G = L.G;
-    const float* qg = (const float*)io.q + (size_t)u * G * D;
-    for (int i = threadIdx.x; i < GM * D; i += 64) s_q[i] = i < G * D ? qg[i] : 0.0f;  // heads past G: zero
-    for (int i = threadIdx.x; i < D; i += 64) {
-        s_kn[i] = ((const float*)io.k_new)[(size_t)u * D + i];
-        s_vn[i] = ((const float*)io.v_new)[(size_t)u * D + i];
-    }
-    __syncthreads();
-    f32_split<D, GM>(L, io, scale_log2, u, split, s_q, s_kn, s_vn, s_p,
-                     L.part + ((size_t)u * nsplit + split) * G * (D + 2), L.score + (size_t)u * L.S * (L.agg ? G : 1));
-}
-
-// head slots of the fp32 step kernel instance for a group of G heads
-constexpr int f32_head_slots(int G) { return G <= 4 ? 4 : G <= 8 ? 8 : 16; }
-
-// LDS of the fused fp32 step kernel with nw wavefronts: the queries, each
-// wavefront's weights and partial, the slot arrays (score, state, ts, lid)
-size_t f32_fused_lds(int GM, int G, int D, int S, int nw) {
-    return (size_t)(GM + 2) * D * 4 + (size_t)nw * GM * 64 * 4 + (size_t)nw * G * (D + 2) * 4 + (size_t)S * 20;
-}
-
-// Step kernel, fp32 pools of head_dim 64, one workgroup per unit (L.nsplit
-// <= 8 wavefronts, one per split): the splits' attention and page scores as
-// above, into LDS;
-// then, as the epilogue kernel does for split plans, the top-r refresh by the
-// whole workgroup, the eviction by wavefront 0 while the others merge the
-// wavefronts' partial outputs, and the state out. One launch per step.
-template <int D, int GM>
-__global__ __launch_bounds__(512) void k_step_f32_fused(LayerView L, StepIO io, float scale_log2, double r) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ RetShared ret;
-    __shared__ int s_aux[260];
-    const int u = blockIdx.x, tid = threadIdx.x, nth = blockDim.x, w = tid >> 6, nw = nth >> 6;
-    if (io.active != nullptr && io.active[u / L.nkv] == 0) return;
-    const int G = L.G, S = L.S;
-    float* s_q = reinterpret_cast<float*>(smem);                       // [GM][D]
-    float* s_kn = s_q + GM * D;                                        // [D] the new token's key
-    float* s_vn = s_kn + D;                                            // [D] and value
-    float (*s_p)[64] = reinterpret_cast<float (*)[64]>(s_vn + D);      // [nw][GM][64]
-    float* s_part = s_vn + D + (size_t)nw * GM * 64;                   // [nw][G][D+2]
-    double* s_score = reinterpret_cast<double*>(s_part + (size_t)nw * G * (D + 2));  // [S] (8-byte aligned)
-    int* s_state = reinterpret_cast<int*>(s_score + S);
-    int* s_ts = s_state + S;
-    int* s_lid = s_ts + S;
-    const UnitRec ur = read_unit(L, u);
-    load_slots(L, u, ur, s_score, s_state, s_ts, s_lid);  // every score +inf until its page is scored
-    const float* qg = (const float*)io.q + (size_t)u * G * D;
-    for (int i = tid; i < GM * D; i += nth) s_q[i] = i < G * D ? qg[i] : 0.0f;  // heads past G: zero
-    for (int i = tid; i < D; i += nth) {
-        s_kn[i] = ((const float*)io.k_new)[(size_t)u * D + i];
-        s_vn[i] = ((const float*)io.v_new)[(size_t)u * D + i];
-    }
-    __syncthreads();
-    f32_split<D, GM>(L, io, scale_log2, u, w, s_q, s_kn, s_vn, s_p + (size_t)w * GM, s_part + (size_t)w * G * (D + 2),
-                     s_score);
-    __syncthreads();
-    refresh_block(L, ur, r, s_score, s_state, s_ts, s_aux, tid, nth, L.dbase);
-    __syncthreads();
-    if (tid < 64) evict_wave(L, ur, s_state, s_ts, s_lid, ret);
-    for (int idx = tid; idx < G * D; idx += nth) {  // merge: out = sum_w 2^(M_w - M) O_w / sum_w 2^(M_w - M) L_w
-        const int h = idx / D, c = idx - (idx / D) * D;
-        float M = -INFINITY;
-        for (int ww = 0; ww < nw; ++ww) M = fmaxf(M, s_part[((size_t)ww * G + h) * (D + 2) + D]);
-        float O = 0.0f, Ls = 0.0f;
-        for (int ww = 0; ww < nw; ++ww) {
-            const float* pw = s_part + ((size_t)ww * G + h) * (D + 2);
-            const float wt = (pw[D] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(pw[D] - M);
-            O += wt * pw[c];
-            Ls += wt * pw[D + 1];
-        }
-        ((float*)io.out)[((size_t)u * G + h) * D + c] = O / Ls;
-    }
-    __syncthreads();
-    retention_store(L, io, u, ur, s_state, s_ts, s_lid, ret, tid, nth);
+// fp32 pools; G4: groups of up to 4 heads (attend_block_f32)
+template <int D, int NW, bool AGG, int LM, bool NT, bool SPLIT, bool G4>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_f32(
+    LayerView L, StepIO io, float scale_log2, double r) {
+    step_item<float, D, NW, AGG, LM, NT, SPLIT, G4>(L, io, scale_log2, r, blockIdx.x);
 }
 
 // Quest on the prompt pages (pools with a prompt region): for one unit, each
@@ -2238,13 +2008,6 @@ __global__ __launch_bounds__(512) void k_step_f32_fused(LayerView L, StepIO io, 
 // prompt pages) and the unit's block list: the prompt blocks holding a
 // chosen page, ascending, then every block of the decode region. One
 // workgroup per unit: 256 threads, 1024 when there are fewer units than CUs.
-template <typename T>
-__device__ __forceinline__ float vec_elem(const u32x4& x, int e);
-template <>
-__device__ __forceinline__ float vec_elem<uint16_t>(const u32x4& x, int e) { return bf2f(u16_at(x, e)); }
-template <>
-__device__ __forceinline__ float vec_elem<float>(const u32x4& x, int e) { return __uint_as_float(x[e]); }
-
 // GQ: the query group size G, a compile-time constant so that the head loop
 // unrolls into straight-line fused multiply-adds.
 
@@ -2490,9 +2253,9 @@ __global__ __launch_bounds__(NW * 64) void k_prompt_select_mfma(LayerView L, Ste
                 const int c = c0 + (lane >> 3);
                 const bool act = c < nc;
                 const int p = act ? s_cand[c] : 0;
-                ScoreFrag<D> f;
-                score_issue<D>(L, u, p, lane & 7, act, f);
-                const double sc = score_finish<D>(L, u, p, lane & 7, act, f, false, false, nullptr, s_qf, nullptr);
+                ScoreFrag<uint16_t, D> f;
+                score_issue<uint16_t, D>(L, u, p, lane & 7, act, f);
+                const double sc = score_finish<uint16_t, D>(L, u, p, lane & 7, act, f, false, false, nullptr, s_qf, nullptr);
                 if (act && (lane & 7) == 0) s_ex[c] = sc;
             }
             __syncthreads();
@@ -2542,25 +2305,6 @@ __global__ __launch_bounds__(NW * 64) void k_prompt_select_mfma(LayerView L, Ste
     }
 }
 
-// Epilogue kernel of the fp32 pools' split path: the rest of the step
-// (finish_units) once the step kernel's launch has ended. One workgroup per
-// decision.
-__global__ __launch_bounds__(1024) void k_epilogue_f32(LayerView L, StepIO io, double r) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ RetShared ret;
-    __shared__ int s_aux[261];
-    const int nu = L.hgrp, u0 = blockIdx.x * nu, tid = threadIdx.x, nth = blockDim.x;
-    if (io.active != nullptr && io.active[u0 / L.nkv] == 0) return;
-    for (int uh = 0; nu > 1 && uh < nu; ++uh) {
-        const MergeFirst mf = merge_first(L, u0 + uh, tid);
-        merge_stage(L, u0 + uh, mf, reinterpret_cast<float*>(smem), tid, nth);
-        __syncthreads();
-        merge_out<float>(L, io, u0 + uh, mf, reinterpret_cast<float*>(smem), tid, nth);
-        __syncthreads();
-    }
-    finish_units<float>(L, io, r, u0, nu, nu == 1, smem, s_aux, ret, tid, nth);
-}
-
 inline unsigned grid1d(size_t n, int block) { return (unsigned)((n + block - 1) / block); }
 
 // LDS of the step kernel: the queries in fp32, the attention wavefronts'
@@ -2572,14 +2316,16 @@ size_t step_lds(int G, int D, int S, int NW, bool fused, int agg, int list_ints)
     return b + (size_t)list_ints * 4;
 }
 
-// Every instance of the bf16 step kernel for one head_dim and workgroup size.
-// f(pointer, ...) is called for the one that the layer and plan ask for, or
-// (all) for each.
-template <int D, int NW, class F>
-void each_step_bf16(bool all, bool agg, int lm, bool nt, bool split, F&& f) {
+// Every instance of the step kernel for one type, head_dim and workgroup size.
+// f(pointer) is called for the one that the layer and plan ask for, or (all)
+// for each.
+template <typename T, int D, int NW, bool G4, class F>
+void each_step(bool all, bool agg, int lm, bool nt, bool split, F&& f) {
     auto one = [&](auto A, auto M, auto N, auto P) {
-        if (all || (agg == A.value && lm == M.value && nt == N.value && split == P.value))
-            f(k_step_bf16<D, NW, A.value, M.value, N.value, P.value>);
+        if (all || (agg == A.value && lm == M.value && nt == N.value && split == P.value)) {
+            if constexpr (sizeof(T) == 2) f(k_step_bf16<D, NW, A.value, M.value, N.value, P.value>);
+            else f(k_step_f32<D, NW, A.value, M.value, N.value, P.value, G4>);
+        }
     };
     auto nts = [&](auto A, auto M, auto P) {
         one(A, M, std::false_type{}, P);
@@ -2592,8 +2338,9 @@ void each_step_bf16(bool all, bool agg, int lm, bool nt, bool split, F&& f) {
     const std::false_type no{};
     nts(no, m0, no);
     nts(no, m0, yes);
-    nts(no, m1, yes);  // (a fused plan without the softmax aggregation selects in the step)
-    nts(no, m2, no);
+    nts(no, m1, yes);
+    if constexpr (sizeof(T) == 2) nts(no, m2, no);  // (a fused bf16 plan without the softmax aggregation selects in the step)
+    else nts(no, m1, no);
     nts(yes, m0, no);
     nts(yes, m0, yes);
     nts(yes, m1, no);
@@ -2602,57 +2349,80 @@ void each_step_bf16(bool all, bool agg, int lm, bool nt, bool split, F&& f) {
 
 }  // namespace
 
-template <int D, int NW>
-hipError_t launch_step_bf16(const LayerView& L, const StepIO& io, const StepPlan& pl, float sl2, double r,
+template <typename T, int D, int NW, bool G4>
+hipError_t launch_step_inst(const LayerView& L, const StepIO& io, const StepPlan& pl, float sl2, double r,
                             hipStream_t s) {
     const int lm = pl.select_in_step ? 2 : L.topk >= 0 ? 1 : 0;
-    each_step_bf16<D, NW>(false, L.agg != 0, lm, L.nt != 0, !pl.fused, [&](auto* kernel) {
+    each_step<T, D, NW, G4>(false, L.agg != 0, lm, L.nt != 0, !pl.fused, [&](auto* kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(L.U * pl.nsplit)), dim3(NW * 64), pl.lds, s, L, io, sl2, r);
     });
     return hipGetLastError();
 }
 
-template <int D, int NW>
+template <typename T, int D, int NW, bool G4>
 hipError_t allow_lds_all(int bytes) {
     hipError_t e = hipSuccess;
-    each_step_bf16<D, NW>(true, false, 0, false, false, [&](auto* kernel) {
+    each_step<T, D, NW, G4>(true, false, 0, false, false, [&](auto* kernel) {
         hipError_t r = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (r != hipSuccess) e = r;
     });
     return e;
 }
 
-// This file is compiled once for each RAAS_PART (in parallel): parts 1 to 6
-// hold the instances of the bf16 step kernel, part 0 everything else.
+// This file is compiled once for each RAAS_PART (in parallel): parts 1 and up
+// hold the instances of the step kernel, part 0 everything else.
 #if RAAS_PART == 0
-#define RAAS_STEP(D, NW)                                                                                        \
-    extern template hipError_t launch_step_bf16<D, NW>(const LayerView&, const StepIO&, const StepPlan&, float, \
-                                                       double, hipStream_t);                                    \
-    extern template hipError_t allow_lds_all<D, NW>(int);
-RAAS_STEP(128, 8)
-RAAS_STEP(128, 4)
-RAAS_STEP(128, 2)
-RAAS_STEP(64, 8)
-RAAS_STEP(64, 4)
-RAAS_STEP(64, 2)
+#define RAAS_STEP(T, D, NW, G4)                                                                                 \
+    extern template hipError_t launch_step_inst<T, D, NW, G4>(const LayerView&, const StepIO&, const StepPlan&, \
+                                                              float, double, hipStream_t);                      \
+    extern template hipError_t allow_lds_all<T, D, NW, G4>(int);
 #else
-#define RAAS_STEP(D, NW)                                                                                         \
-    template hipError_t launch_step_bf16<D, NW>(const LayerView&, const StepIO&, const StepPlan&, float, double, \
-                                                hipStream_t);                                                    \
-    template hipError_t allow_lds_all<D, NW>(int);
-#if RAAS_PART == 1
-RAAS_STEP(128, 8)
-#elif RAAS_PART == 2
-RAAS_STEP(128, 4)
-#elif RAAS_PART == 3
-RAAS_STEP(128, 2)
-#elif RAAS_PART == 4
-RAAS_STEP(64, 8)
-#elif RAAS_PART == 5
-RAAS_STEP(64, 4)
-#elif RAAS_PART == 6
-RAAS_STEP(64, 2)
+#define RAAS_STEP(T, D, NW, G4)                                                                                   \
+    template hipError_t launch_step_inst<T, D, NW, G4>(const LayerView&, const StepIO&, const StepPlan&, float,   \
+                                                       double, hipStream_t);                                      \
+    template hipError_t allow_lds_all<T, D, NW, G4>(int);
 #endif
+#if RAAS_PART == 0 || RAAS_PART == 1
+RAAS_STEP(uint16_t, 128, 8, false)
+#endif
+#if RAAS_PART == 0 || RAAS_PART == 2
+RAAS_STEP(uint16_t, 128, 4, false)
+#endif
+#if RAAS_PART == 0 || RAAS_PART == 3
+RAAS_STEP(uint16_t, 128, 2, false)
+#endif
+#if RAAS_PART == 0 || RAAS_PART == 4
+RAAS_STEP(uint16_t, 64, 8, false)
+#endif
+#if RAAS_PART == 0 || RAAS_PART == 5
+RAAS_STEP(uint16_t, 64, 4, false)
+#endif
+#if RAAS_PART == 0 || RAAS_PART == 6
+RAAS_STEP(uint16_t, 64, 2, false)
+#endif
+#if RAAS_PART == 0 || RAAS_PART == 7
+RAAS_STEP(float, 128, 8, false)
+#endif
+#if RAAS_PART == 0 || RAAS_PART == 8
+RAAS_STEP(float, 128, 8, true)
+#endif
+#if RAAS_PART == 0 || RAAS_PART == 9
+RAAS_STEP(float, 128, 4, false)
+#endif
+#if RAAS_PART == 0 || RAAS_PART == 10
+RAAS_STEP(float, 128, 4, true)
+#endif
+#if RAAS_PART == 0 || RAAS_PART == 11
+RAAS_STEP(float, 64, 8, false)
+#endif
+#if RAAS_PART == 0 || RAAS_PART == 12
+RAAS_STEP(float, 64, 8, true)
+#endif
+#if RAAS_PART == 0 || RAAS_PART == 13
+RAAS_STEP(float, 64, 4, false)
+#endif
+#if RAAS_PART == 0 || RAAS_PART == 14
+RAAS_STEP(float, 64, 4, true)
 #endif
 
 #if RAAS_PART == 0
@@ -2674,7 +2444,10 @@ RAAS_STEP(64, 2)
 // kFusedBlocksHalf (128 units: 64 blocks 34.4 / 35.9, 128 blocks 60.6 / 59.5,
 // 256 blocks 95.4 / 91.1). More than kSplits splits, or fewer than 8 blocks in
 // one, no longer help (8 units: 64 blocks 15.1 in 8 and 15.3 in 16; 256 blocks
-// 26.1 in 4, 21.3 in 8, 19.2 in 16, 21.0 in 32).
+// 26.1 in 4, 21.3 in 8, 19.2 in 16, 21.0 in 32). An fp32 block costs more
+// arithmetic, so fp32 units split at half as many (8 units, 32 blocks 18.9 /
+// 14.2; 64 units 22.0 / 18.8; 128 units, 32 blocks 25.5 / 27.0, 64 blocks 38.6
+// / 37.5).
 constexpr int kFusedBlocks = 32;
 constexpr int kHalfUnits = 113;
 constexpr int kFusedBlocksHalf = 64;
@@ -2701,81 +2474,66 @@ constexpr int kFusedPromptPages = 512;
 constexpr int kSmallWorkUnits = 1024;
 constexpr int kSmallWorkBlocks = 32;
 
-StepPlan plan_step(int U, int G, int D, int S, int Lcap, int ps, int work_blocks, bool bf16, int agg,
+StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool bf16, int agg,
                    bool grouped, int list_ints, int split_override, int npr, int nkv,
                    bool fixed_scratch) {
-    (void)ps;
     StepPlan pl{};
     const int nblk = Lcap / kBlockTokens;
+    // blocks of 16 KB (head_dim 128): 32 tokens in bf16, 16 in fp32
+    const int blocks = bf16 ? nblk : 2 * nblk, work = bf16 ? work_blocks : 2 * work_blocks;
     int want;
-    if (!bf16) {
-        pl.waves = 1;
-        want = split_override > 0 ? split_override : (nblk + 1) / 2;
-    } else {
+    pl.waves = bf16 ? 2 : 4;
+    for (int nw : {8, 4}) {
+        if (step_lds(G, D, S, nw, false, agg, list_ints) <= kMaxLds) {
+            pl.waves = nw;
+            break;
+        }
+    }
+    // more units than CUs: workgroups of 4 wavefronts, two per CU, so that
+    // one unit's serial phases (staging, selection, retention) overlap
+    // another's streaming, and up to 512 units run in one round (288 units,
+    // L 1024: 45.4 -> 39.0 us; 352 units, L 8192: 254 -> 242; 504 units,
+    // L 2048: 90.5 -> 87.5)
+    if (split_override <= 0 && U > 256 && pl.waves == 8 &&
+        2 * step_lds(G, D, S, 4, !grouped, agg, list_ints) <= kMaxLds)
+        pl.waves = 4;
+    // four or more units per CU, each with little to stream: four
+    // workgroups per CU overlap more units' serial phases
+    if (split_override <= 0 && bf16 && !grouped && U >= kSmallWorkUnits && work <= kSmallWorkBlocks &&
+        pl.waves == 4 && 4 * step_lds(G, D, S, 2, true, agg, list_ints) <= kMaxLds)
         pl.waves = 2;
-        for (int nw : {8, 4, 2}) {
-            if (step_lds(G, D, S, nw, false, agg, list_ints) <= kMaxLds) {
-                pl.waves = nw;
-                break;
-            }
-        }
-        // more units than CUs: workgroups of 4 wavefronts, two per CU, so that
-        // one unit's serial phases (staging, selection, retention) overlap
-        // another's streaming, and up to 512 units run in one round (288 units,
-        // L 1024: 45.4 -> 39.0 us; 352 units, L 8192: 254 -> 242; 504 units,
-        // L 2048: 90.5 -> 87.5)
-        if (split_override <= 0 && U > 256 && pl.waves == 8 &&
-            2 * step_lds(G, D, S, 4, !grouped, agg, list_ints) <= kMaxLds)
-            pl.waves = 4;
-        // four or more units per CU, each with little to stream: four
-        // workgroups per CU overlap more units' serial phases
-        if (split_override <= 0 && !grouped && U >= kSmallWorkUnits && work_blocks <= kSmallWorkBlocks &&
-            pl.waves == 4 && 4 * step_lds(G, D, S, 2, true, agg, list_ints) <= kMaxLds)
-            pl.waves = 2;
-        const bool fits = !grouped && step_lds(G, D, S, pl.waves, true, agg, list_ints) <= kMaxLds;
-        const int fused_blocks = U < kHalfUnits ? kFusedBlocks : kFusedBlocksHalf;
-        if (split_override > 0) {
-            want = split_override;
-        } else if (fits && fixed_scratch &&
-                   (nblk <= kFusedBlocksPerWave * pl.waves ||
-                    (S <= kFewSlots && nblk <= kFusedBlocksPerWaveFewSlots * pl.waves))) {
-            want = 1;
-        } else if (fits && list_ints > 0 && !agg && U < 256 && npr <= kFusedPromptPages &&
-                   work_blocks <= kFusedPromptBlocksPerWave * pl.waves) {
-            // a short prompt region: the fused workgroup chooses its prompt
-            // pages itself and attends the chosen blocks and the decode ones,
-            // which saves the selection kernel's launch as well
-            want = 1;
-        } else if (fits && work_blocks <= fused_blocks && (list_ints == 0 || agg || npr <= kFusedPromptPages)) {
-            want = 1;
-        } else {
-            want = std::min(std::min(std::max(256 / U, 1), kSplits), (work_blocks + 7) / 8);
-        }
+    const bool fits = !grouped && step_lds(G, D, S, pl.waves, true, agg, list_ints) <= kMaxLds;
+    const int fused_blocks = (U < kHalfUnits ? kFusedBlocks : kFusedBlocksHalf) / (bf16 ? 1 : 2);
+    if (split_override > 0) {
+        want = split_override;
+    } else if (fits && fixed_scratch &&
+               (blocks <= kFusedBlocksPerWave * pl.waves ||
+                (S <= kFewSlots && blocks <= kFusedBlocksPerWaveFewSlots * pl.waves))) {
+        want = 1;
+    } else if (fits && bf16 && list_ints > 0 && !agg && U < 256 && npr <= kFusedPromptPages &&
+               work <= kFusedPromptBlocksPerWave * pl.waves) {
+        // a short prompt region: the fused workgroup chooses its prompt
+        // pages itself and attends the chosen blocks and the decode ones,
+        // which saves the selection kernel's launch as well
+        want = 1;
+    } else if (fits && work <= fused_blocks && (list_ints == 0 || agg || !bf16 || npr <= kFusedPromptPages)) {
+        want = 1;
+    } else {
+        want = std::min(std::min(std::max(256 / U, 1), kSplits), (work + 7) / 8);
     }
     want = want < 1 ? 1 : want;
     want = want > kMaxSplits ? kMaxSplits : want;
     want = want > nblk ? nblk : want;
     pl.bps = (nblk + want - 1) / want;
     pl.nsplit = (nblk + pl.bps - 1) / pl.bps;
-    if (bf16) {
-        // (fused, a step with fewer units than CUs would bound a long prompt
-        // region on one CU per unit: the selection kernels do that faster)
-        const bool long_prompt = list_ints > 0 && !agg && U < 256 && npr > kFusedPromptPages;
-        pl.fused = !grouped && !long_prompt && pl.nsplit == 1 &&
-                   step_lds(G, D, S, pl.waves, true, agg, list_ints) <= kMaxLds;
-        pl.lds = step_lds(G, D, S, pl.waves, pl.fused, agg, list_ints);
-        // (the workgroup that finishes a split unit reuses the step's LDS)
-        if (!pl.fused) pl.lds = std::max(pl.lds, finish_lds(G, S, pl.nsplit, agg, grouped ? nkv : 1));
-    } else {
-        // fp32: one workgroup per unit with a wavefront per split (up to 8,
-        // two per SIMD at the kernel's registers), which then runs the
-        // epilogue itself; the softmax aggregation, the sequence scope, a
-        // prompt region and head_dim 128 (whose key rows would spill the
-        // fused kernel's registers) keep the epilogue kernel
-        pl.fused = D == 64 && !grouped && !agg && list_ints == 0 && pl.nsplit <= 8 &&
-                   f32_fused_lds(f32_head_slots(G), G, D, S, pl.nsplit) <= kMaxLds;
-        pl.lds = pl.fused ? f32_fused_lds(f32_head_slots(G), G, D, S, pl.nsplit) : 0;
-    }
+    // (fused, a bf16 step with fewer units than CUs would bound a long prompt
+    // region on one CU per unit: the selection kernels do that faster)
+    const bool long_prompt = bf16 && list_ints > 0 && !agg && U < 256 && npr > kFusedPromptPages;
+    pl.fused = !grouped && !long_prompt && pl.nsplit == 1 &&
+               step_lds(G, D, S, pl.waves, true, agg, list_ints) <= kMaxLds;
+    pl.lds = step_lds(G, D, S, pl.waves, pl.fused, agg, list_ints);
+    // (the workgroup that finishes a split unit reuses the step's LDS)
+    if (!pl.fused) pl.lds = std::max(pl.lds, finish_lds(G, S, pl.nsplit, agg, grouped ? nkv : 1));
     // a fused workgroup covers its unit, so it can choose the prompt pages
     // itself (the softmax aggregation keeps the selection kernel)
     pl.select_in_step = bf16 && pl.fused && list_ints > 0 && !agg;
@@ -2785,15 +2543,15 @@ StepPlan plan_step(int U, int G, int D, int S, int Lcap, int ps, int work_blocks
 hipError_t allow_large_lds() {
     const int bytes = (int)kMaxLds;
     hipError_t e = hipSuccess;
-    for (hipError_t r : {allow_lds_all<128, 8>(bytes), allow_lds_all<128, 4>(bytes), allow_lds_all<128, 2>(bytes),
-                         allow_lds_all<64, 8>(bytes), allow_lds_all<64, 4>(bytes), allow_lds_all<64, 2>(bytes)})
+    for (hipError_t r :
+         {allow_lds_all<uint16_t, 128, 8, false>(bytes), allow_lds_all<uint16_t, 128, 4, false>(bytes),
+          allow_lds_all<uint16_t, 128, 2, false>(bytes), allow_lds_all<uint16_t, 64, 8, false>(bytes),
+          allow_lds_all<uint16_t, 64, 4, false>(bytes), allow_lds_all<uint16_t, 64, 2, false>(bytes),
+          allow_lds_all<float, 128, 8, false>(bytes), allow_lds_all<float, 128, 8, true>(bytes),
+          allow_lds_all<float, 128, 4, false>(bytes), allow_lds_all<float, 128, 4, true>(bytes),
+          allow_lds_all<float, 64, 8, false>(bytes), allow_lds_all<float, 64, 8, true>(bytes),
+          allow_lds_all<float, 64, 4, false>(bytes), allow_lds_all<float, 64, 4, true>(bytes)})
         if (r != hipSuccess) e = r;
-    for (const void* f : {(const void*)k_step_f32_fused<64, 4>, (const void*)k_step_f32_fused<64, 8>,
-                          (const void*)k_step_f32_fused<64, 16>}) {
-        hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-        if (r != hipSuccess) e = r;
-    }
-
     return e;
 }
 
@@ -2874,53 +2632,24 @@ hipError_t launch_prefill(const LayerView& L, const void* k, const void* v, cons
     return hipGetLastError();
 }
 
-// fp32 step kernel with room for GM >= G query heads (the head loops unroll
-// GM times: a small bound keeps the kernel's code small)
-template <int D, int GM>
-void launch_step_f32_gm(const LayerView& L, const StepIO& io, const StepPlan& pl, float sl2, double r, hipStream_t s) {
-    if constexpr (D == 64) {
-        if (pl.fused) {
-            hipLaunchKernelGGL((k_step_f32_fused<D, GM>), dim3((unsigned)L.U), dim3(64 * pl.nsplit), pl.lds, s, L, io,
-                               sl2, r);
-            return;
-        }
-    }
-    hipLaunchKernelGGL((k_step_f32<D, GM>), dim3((unsigned)(L.U * pl.nsplit)), dim3(64), 0, s, L, io, sl2);
-}
-
-template <int D>
-void launch_step_f32(const LayerView& L, const StepIO& io, const StepPlan& pl, float sl2, double r, hipStream_t s) {
-    if (L.G <= 4) launch_step_f32_gm<D, 4>(L, io, pl, sl2, r, s);
-    else if (L.G <= 8) launch_step_f32_gm<D, 8>(L, io, pl, sl2, r, s);
-    else launch_step_f32_gm<D, 16>(L, io, pl, sl2, r, s);
-}
-
-hipError_t launch_step(const LayerView& L, const StepIO& io, const StepPlan& pl, double r, hipStream_t s) {
+hipError_t launch_step(const LayerView& L, const StepIO& io, const StepPlan& plan, double r, hipStream_t s) {
     const float sl2 = (float)(1.4426950408889634 / sqrt((double)L.D));
-    if (!L.bf16) {
-        if (L.D == 128) launch_step_f32<128>(L, io, pl, sl2, r, s);
-        else launch_step_f32<64>(L, io, pl, sl2, r, s);
-        return hipGetLastError();
-    }
-    if (L.D == 128) {
-        switch (pl.waves) {
-            case 8: return launch_step_bf16<128, 8>(L, io, pl, sl2, r, s);
-            case 4: return launch_step_bf16<128, 4>(L, io, pl, sl2, r, s);
-            default: return launch_step_bf16<128, 2>(L, io, pl, sl2, r, s);
-        }
-    }
-    switch (pl.waves) {
-        case 8: return launch_step_bf16<64, 8>(L, io, pl, sl2, r, s);
-        case 4: return launch_step_bf16<64, 4>(L, io, pl, sl2, r, s);
-        default: return launch_step_bf16<64, 2>(L, io, pl, sl2, r, s);
-    }
-}
-
-hipError_t launch_epilogue(const LayerView& L, const StepIO& io, double r, hipStream_t stream) {
-    const dim3 grid((unsigned)(L.U / L.hgrp));
-    const dim3 block(grid.x < 256 ? 1024 : 256);  // fewer workgroups than CUs: more threads each
-    hipLaunchKernelGGL(k_epilogue_f32, grid, block, finish_lds(L.G, L.S, L.nsplit, L.agg, L.hgrp), stream, L, io, r);
-    return hipGetLastError();
+    auto waves = [&](auto d, auto t, auto g4) {
+        using T = decltype(t);
+        constexpr int D = decltype(d)::value;
+        constexpr bool G4 = decltype(g4)::value;
+        if (plan.waves == 8) return launch_step_inst<T, D, 8, G4>(L, io, plan, sl2, r, s);
+        if constexpr (sizeof(T) == 2)
+            if (plan.waves == 2) return launch_step_inst<T, D, 2, G4>(L, io, plan, sl2, r, s);
+        return launch_step_inst<T, D, 4, G4>(L, io, plan, sl2, r, s);
+    };
+    const std::integral_constant<int, 128> d128{};
+    const std::integral_constant<int, 64> d64{};
+    const std::true_type yes{};
+    const std::false_type no{};
+    if (L.bf16) return L.D == 128 ? waves(d128, uint16_t{}, no) : waves(d64, uint16_t{}, no);
+    if (L.G <= 4) return L.D == 128 ? waves(d128, float{}, yes) : waves(d64, float{}, yes);
+    return L.D == 128 ? waves(d128, float{}, no) : waves(d64, float{}, no);
 }
 
 #endif  // RAAS_PART == 0

@@ -36,7 +36,7 @@ raas_status hip_fail(hipError_t e, const char* what) {
     return fail(RAAS_E_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
-constexpr int kKernels = 3;  // step kernel, epilogue kernel, prompt selection kernel
+constexpr int kKernels = 3;  // step kernel, (none), prompt selection kernel
 constexpr size_t kProfRing = 8192;
 
 struct Timing {
@@ -300,7 +300,7 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
         const int per_page = std::max(1, p->ps / kBlockTokens);
         work_blocks = L.nblk - nbp + std::min(nbp, p->cfg.prompt_topk * per_page);
     }
-    const StepPlan pl = plan_step(p->U, p->G, p->D, p->S, L.nblk * kBlockTokens, p->ps, work_blocks,
+    const StepPlan pl = plan_step(p->U, p->G, p->D, p->S, L.nblk * kBlockTokens, work_blocks,
                                   p->cfg.dtype == RAAS_BF16, p->cfg.score_aggregation,
                                   p->cfg.decision_scope == RAAS_SCOPE_SEQUENCE, list_ints(p), p->split_override, p->npr,
                                   p->cfg.n_kv_heads, fixed_scratch);
@@ -311,7 +311,7 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
     // wavefronts streams at least 8 blocks each (batch 32 at L 2048: 40.79 ->
     // 40.38 us, the Qwen stack and L 8192 level) and not below (batch 1 at
     // L 1024 +0.14 us; batch 128 at L 512, 2 wavefronts, +0.23 us)
-    L.early = pl.waves == 8 && (pl.nsplit > 1 || L.nblk >= 8 * pl.waves) ? 1 : 0;
+    L.early = pl.waves == 8 && (pl.nsplit > 1 || L.nblk * (L.bf16 ? 1 : 2) >= 8 * pl.waves) ? 1 : 0;
     const bool select_kernel = p->npr > 0 && !pl.select_in_step;
     if (fixed_scratch) {
         const size_t U = (size_t)p->U, S = (size_t)p->S;
@@ -364,12 +364,6 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
     hipError_t e = launch_step(L, io, pl, p->cfg.r, s);
     if (prof) prof_record(p, 0, false, s);
     if (e != hipSuccess) return hip_fail(e, "step launch");
-    if (!pl.fused && p->cfg.dtype != RAAS_BF16) {
-        if (prof) prof_record(p, 1, true, s);
-        e = launch_epilogue(L, io, p->cfg.r, s);
-        if (prof) prof_record(p, 1, false, s);
-        if (e != hipSuccess) return hip_fail(e, "epilogue launch");
-    }
     p->descending[layer] ^= 1;
     p->steps[layer] += 1;
     p->last_stream = s;

@@ -551,6 +551,37 @@ def test_split_unit_finish(case):
     assert rep.evictions > 0
 
 
+# fp32 pools: both forms of the matrix product (up to 4 heads, more) at the
+# edges of their columns, each head_dim, every position of a token in a
+# 16-token block (page 8 and 16, odd prompts), fused and split, workgroups of
+# 4 wavefronts (more units than CUs), prompt regions by block lists.
+F32_CASES = [
+    dict(n_q_heads=2, n_kv_heads=2),                                   # G = 1
+    dict(n_q_heads=8, n_kv_heads=2, page_size=8, prefill_len=37),      # G = 4
+    dict(n_q_heads=10, n_kv_heads=2),                                  # G = 5
+    dict(n_q_heads=32, n_kv_heads=2, prefill_len=0),                   # G = 16
+    dict(n_q_heads=6, n_kv_heads=2, head_dim=64, page_size=8),         # G = 3
+    dict(n_q_heads=14, n_kv_heads=2, head_dim=64, prefill_len=33),     # G = 7
+    dict(budget=512, splits=3),
+    dict(budget=512, splits=17, n_q_heads=12, n_kv_heads=2),
+    dict(batch=130, n_kv_heads=2, budget=64, page_size=8, decode_steps=120),
+    dict(prompt_tokens=192, prompt_topk=4, prefill_len=190),
+    dict(prompt_tokens=192, prompt_topk=4, prefill_len=181, splits=2, n_q_heads=10, n_kv_heads=2),
+    dict(prompt_tokens=192, prompt_topk=4, prefill_len=190, aggregation=1, head_dim=64),
+]
+
+
+@pytest.mark.parametrize("case", F32_CASES, ids=[",".join("%s=%s" % kv for kv in c.items()) for c in F32_CASES])
+def test_f32_blocks(case):
+    case = dict(case)
+    run_kw = {k: case.pop(k) for k in ("splits", "aggregation", "prompt_tokens", "prompt_topk") if k in case}
+    w = small(dtype="f32", decode_steps=case.pop("decode_steps", max(300, case.get("budget", 128) + 40)), **case)
+    _say("case fp32 blocks %s %s" % (case, run_kw))
+    rep = run_parity(w, seed=23, steps=w.decode_steps, out_every=3, **run_kw)
+    _report(rep, "fp32-blocks")
+    assert rep.evictions > 0
+
+
 # One page table per (sequence, layer) shared by its KV heads (decision
 # scope 1), against the oracle's grouped step; (aggregation, rank_pinned).
 SCOPE_VARIANTS = [(0, False), (1, False), (0, True)]
