@@ -161,9 +161,10 @@ raas_status raas_prefill(raas_pool* pool, int32_t layer, const void* k, const vo
  * raas_prefill it may be called again at any time: a selected sequence
  * starts over with the new prompt (its pages freed, its clock reset), which
  * is how a finished request's place in the batch is reused. The first
- * prefill of a layer must cover every sequence (else RAAS_E_STATE). The
- * lengths reach the device through a pinned buffer of the pool; a call first
- * waits for the previous ragged prefill's copy out of it. Errors:
+ * prefill of a layer must cover every sequence (else RAAS_E_STATE). With
+ * more than 256 sequences the lengths reach the device through a pinned
+ * buffer of the pool, and a call first waits for the previous ragged
+ * prefill's copy out of it. Errors:
  * RAAS_E_INVALID, RAAS_E_STATE, RAAS_E_BUDGET (policy RAAS_PREFILL_ERROR and
  * a selected prompt over S-1 pages), RAAS_E_HIP. */
 raas_status raas_prefill_ragged(raas_pool* pool, int32_t layer, const void* k, const void* v,

@@ -65,13 +65,15 @@ struct LayerView {
     int early;          // 1: the first score pass's loads go out before the first block is attended
 };
 
-// Prefill input of one layer: `stride` token rows per unit; per-sequence
-// lengths (lens, device [batch]) or one length P; an optional device mask
-// [batch] of the sequences to (re)initialise.
+// Prefill input of one layer: `stride` token rows per unit; one length P, or
+// (P < 0) per-sequence lengths, -1 for a sequence that keeps its state: in
+// `lens` (device [batch]), or, when that is NULL, in the kernel's arguments,
+// up to kArgSeqs sequences.
+constexpr int kArgSeqs = 256;
 struct PrefillIn {
     const int32_t* lens;
-    const int32_t* mask;
     int P, stride;
+    int32_t arg_lens[kArgSeqs];
 };
 
 struct StepIO {

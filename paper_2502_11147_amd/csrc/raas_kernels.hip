@@ -90,19 +90,25 @@ __device__ __forceinline__ float vec_elem<uint16_t>(const u32x4& x, int e) { ret
 template <>
 __device__ __forceinline__ float vec_elem<float>(const u32x4& x, int e) { return __uint_as_float(x[e]); }
 
+// Makes this wavefront's LDS writes visible to its own later LDS reads (the
+// lanes of one wavefront exchanging data through LDS; no workgroup barrier).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------
 // Prefill (the prefill stage of Algorithm 1's cache store): a unit's first
 // tokens go to pages 0, 1, ..., which are marked pinned; at most S-1 pages
 // are kept (the first ones), so one slot stays for decode pages. Lengths are
-// per sequence (in.lens) or uniform (in.P); in.mask, when given, selects the
-// sequences to (re)initialise and leaves the others as they are. The input
-// holds in.stride rows per unit.
+// per sequence or uniform; sequences that are not selected keep their state.
+// The input holds in.stride rows per unit.
 
 // Prefill length of unit u, or -1 when its sequence is not selected.
 __device__ __forceinline__ int unit_prefill_len(const LayerView& L, const PrefillIn& in, int u) {
     const int seq = u / L.nkv;
-    if (in.mask != nullptr && in.mask[seq] == 0) return -1;
-    return in.lens != nullptr ? in.lens[seq] : in.P;
+    return in.P >= 0 ? in.P : in.lens != nullptr ? in.lens[seq] : in.arg_lens[seq];
 }
 
 // pages kept of a prefill of P tokens: the first min(ceil(P/ps), pcap)
@@ -111,10 +117,8 @@ __device__ __forceinline__ int kept_pages(const LayerView& L, int P) {
     return min((P + L.ps - 1) / L.ps, L.pcap);
 }
 
-__global__ void k_prefill_meta(LayerView L, PrefillIn in) {
-    const int u = blockIdx.x;
-    const int P = unit_prefill_len(L, in, u);
-    if (P < 0) return;
+// Slot and unit records of a unit just prefilled with P tokens.
+__device__ __forceinline__ void prefill_records(const LayerView& L, int u, int P) {
     const int keep_pages = kept_pages(L, P);
     const size_t base = (size_t)u * L.S;
     for (int s = threadIdx.x; s < L.S; s += blockDim.x) {
@@ -136,87 +140,150 @@ __global__ void k_prefill_meta(LayerView L, PrefillIn in) {
     }
 }
 
-// K rows (D/8 threads per token) then V octets (D threads per 8 tokens),
-// over max_tok tokens per unit; tokens past a unit's kept ones are skipped
-// (K) or zero (the rest of V's last octet).
-template <int D>
-__global__ void k_prefill_bf16(LayerView L, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                               PrefillIn in, int max_tok) {
-    const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t nK = (size_t)L.U * max_tok * (D / 8);
-    const int octets = (max_tok + 7) / 8;
-    const size_t nV = (size_t)L.U * octets * D;
-    uint16_t* K = (uint16_t*)L.K;
-    uint16_t* V = (uint16_t*)L.V;
-    if (tid < nK) {
-        const int u = (int)(tid / ((size_t)max_tok * (D / 8)));
-        const int rem = (int)(tid - (size_t)u * max_tok * (D / 8));
-        const int t = rem / (D / 8), ch = rem % (D / 8);
-        const int P = unit_prefill_len(L, in, u);
-        if (t >= min(P, kept_pages(L, P) * L.ps)) return;  // also P < 0: not selected
-        st4(K + (size_t)u * L.Lcap * D + k_off<D>(t, ch * 8), ld4(k + ((size_t)u * in.stride + t) * D + ch * 8));
-    } else if (tid - nK < nV) {
-        const size_t r = tid - nK;
-        const int u = (int)(r / ((size_t)octets * D));
-        const int rem = (int)(r - (size_t)u * octets * D);
-        const int g = rem / D, c = rem % D;
-        const int P = unit_prefill_len(L, in, u);
-        const int keep_tok = min(P, kept_pages(L, P) * L.ps);
-        if (8 * g >= keep_tok) return;
-        uint32_t w[4];
+// Wavefronts of a prefill workgroup.
+constexpr int kPrefillWaves = 4;
+// Tokens of a wavefront's tile: eight per lane, a row of D channels over D /
+// (16 bytes of T) lanes; 8 KB of keys and of values either way.
+template <typename T, int D>
+constexpr int prefill_tile() {
+    return 8 * 64 * 16 / (D * (int)sizeof(T));
+}
+
+// The prefill store, in one launch: keys, values, slot records and (REP, pools
+// that rank or select prompt pages) the kept pages' representative keys. A
+// wavefront takes `tiles` consecutive tiles (more than one only where a page
+// is longer than a tile, so that its representative key stays with one
+// wavefront): a lane reads 16 bytes of each of eight rows, all 16 reads of a
+// tile's keys and values in flight together, whole rows side by side. fp32
+// pools store them as they are. bf16 pools store blocks in operand order: a
+// lane's 8x8 values turn in registers (32 byte permutes), then keys and values
+// pass through LDS in 16-byte pieces, so that every store writes 1 KiB of
+// consecutive bytes. Bound by HBM: one read and one write of the prompt. (The
+// form before read values two bytes at a time and stored keys in 64-byte runs,
+// 3.9 TB/s at 256 units of 1024 tokens, then read every key again for the
+// representative keys, two bytes at a time, 0.4 TB/s.)
+// Tokens past a unit's kept ones are skipped (the rest of the last octet of
+// values is zero).
+template <typename T, int D, bool REP>
+__global__ __launch_bounds__(kPrefillWaves * 64) void k_prefill(LayerView L, const T* __restrict__ k,
+                                                                const T* __restrict__ v, PrefillIn in, int chunks,
+                                                                int tiles) {
+    constexpr bool BF = sizeof(T) == 2;
+    constexpr int V = 16 / sizeof(T), LC = D / V, NO = 64 / LC, TT = 8 * NO;
+    static_assert(TT == prefill_tile<T, D>(), "");
+    __shared__ __align__(16) u32x4 s_piece[BF ? kPrefillWaves : 1][BF ? 512 : 1];
+    const int u = blockIdx.x / chunks, chunk = blockIdx.x - u * chunks;
+    const int P = unit_prefill_len(L, in, u);
+    if (P < 0) return;  // not selected
+    if (chunk == 0) prefill_records(L, u, P);
+    const int keep = min(P, kept_pages(L, P) * L.ps);
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, oct = lane / LC, ch = lane % LC;
+    T* K = (T*)L.K + (size_t)u * L.Lcap * D;
+    T* Vp = (T*)L.V + (size_t)u * L.Lcap * D;
+    const T* ku = k + (size_t)u * in.stride * D + V * ch;
+    const T* vu = v + (size_t)u * in.stride * D + V * ch;
+    const T inf = from_f<T>(INFINITY), ninf = from_f<T>(-INFINITY);
+    T hi[V], lo[V];
 #pragma unroll
-        for (int j = 0; j < 8; j += 2) {
-            const int t0 = 8 * g + j, t1 = t0 + 1;
-            const uint32_t lo = (t0 < keep_tok) ? v[((size_t)u * in.stride + t0) * D + c] : 0u;
-            const uint32_t hi = (t1 < keep_tok) ? v[((size_t)u * in.stride + t1) * D + c] : 0u;
-            w[j / 2] = lo | (hi << 16);
+    for (int e = 0; e < V; ++e) {
+        hi[e] = ninf;
+        lo[e] = inf;
+    }
+    for (int it = 0; it < tiles; ++it) {
+        const int t_tile = ((chunk * kPrefillWaves + w) * tiles + it) * TT;
+        if (t_tile >= keep) break;
+        const int t0 = t_tile + 8 * oct, n = min(max(keep - t0, 0), 8);  // this lane's tokens
+        u32x4 kr[8], vr[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) kr[r] = r < n ? ld4(ku + (size_t)(t0 + r) * D) : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int r = 0; r < 8; ++r) vr[r] = r < n ? ld4(vu + (size_t)(t0 + r) * D) : u32x4{0u, 0u, 0u, 0u};
+        if constexpr (REP) {  // per-channel min and max, the first of equals
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    const float x = vec_elem<T>(kr[r], e);
+                    if (r < n && x > to_f(hi[e])) hi[e] = from_f<T>(x);
+                    if (r < n && x < to_f(lo[e])) lo[e] = from_f<T>(x);
+                }
         }
-        st4(V + (size_t)u * L.Lcap * D + v_off<D>(8 * g, c), u32x4{w[0], w[1], w[2], w[3]});
+        if constexpr (!BF) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+                if (r < n) {
+                    st4(K + (size_t)(t0 + r) * D + V * ch, kr[r]);
+                    st4(Vp + (size_t)(t0 + r) * D + V * ch, vr[r]);
+                }
+        } else {
+            // 16-byte piece p of the tile lies at LDS slot p with its low three
+            // bits turned by the next three: the lanes of a write, eight pieces
+            // apart, fall on different banks, and a read still covers 128-byte runs
+            constexpr int BP = 4 * D;  // pieces of a block
+            u32x4* sp = s_piece[w];
+            auto slot = [](int p) { return p ^ ((p >> 3) & 7); };
+            const int blk = oct >> 2, a = oct & 3;
+#pragma unroll
+            for (int r = 0; r < 8; ++r)  // token 8a + r of the block: see k_off
+                sp[slot(blk * BP + ((r >> 2) * (D / 32) + (ch >> 2)) * 64 + 16 * (ch & 3) + 4 * a + (r & 3))] = kr[r];
+            wave_lds_sync();
+            const size_t out = (size_t)(t_tile >> 5) * 32 * D;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int p = 64 * j + lane, q = p % BP, i = q & 15;
+                const int t = 32 * (p / BP) + 8 * (i >> 2) + 4 * (q / (2 * D)) + (i & 3);
+                if (t_tile + t < keep) st4(K + out + (size_t)p * 8, sp[slot(p)]);
+            }
+            wave_lds_sync();
+            // values: channel e of this lane's eight, its eight tokens side by side
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                u32x4 x;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    x[j] = __builtin_amdgcn_perm(vr[2 * j + 1][e >> 1], vr[2 * j][e >> 1],
+                                                 (e & 1) ? 0x07060302u : 0x05040100u);
+                const int c = 8 * ch + e;  // see v_off
+                sp[slot(blk * BP + (c >> 4) * 64 + 16 * a + (c & 15))] = x;
+            }
+            wave_lds_sync();
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int p = 64 * j + lane;
+                const int t = 32 * (p / BP) + 8 * ((p >> 4) & 3);
+                if (t_tile + t < keep) st4(Vp + out + (size_t)p * 8, sp[slot(p)]);
+            }
+            wave_lds_sync();
+        }
+        if constexpr (REP) {
+            // a page's octets combine (the earlier one's value kept between
+            // equals on the lowest lanes, which store) when the page ends
+            const int po = min(L.ps >> 3, NO);  // octets of a page in a tile
+            const int t_last = t_tile + TT;
+            if ((t_last & (L.ps - 1)) == 0 || L.ps <= TT || t_last >= keep) {
+                for (int d = 1; d < po; d <<= 1)
+#pragma unroll
+                    for (int e = 0; e < V; ++e) {
+                        const float h = __shfl_xor(to_f(hi[e]), d * LC), l = __shfl_xor(to_f(lo[e]), d * LC);
+                        if (h > to_f(hi[e])) hi[e] = from_f<T>(h);
+                        if (l < to_f(lo[e])) lo[e] = from_f<T>(l);
+                    }
+                if ((oct & (po - 1)) == 0 && t0 < keep) {
+                    const size_t o = ((size_t)u * L.S + t0 / L.ps) * D + V * ch;
+                    u32x4 x, y;
+                    __builtin_memcpy(&x, hi, 16);
+                    __builtin_memcpy(&y, lo, 16);
+                    st4((T*)L.kmax + o, x);
+                    st4((T*)L.kmin + o, y);
+                }
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    hi[e] = ninf;
+                    lo[e] = inf;
+                }
+            }
+        }
     }
-}
-
-__global__ void k_prefill_f32(LayerView L, const float* __restrict__ k, const float* __restrict__ v, PrefillIn in,
-                              int max_tok) {
-    const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int D = L.D;
-    const size_t n = (size_t)L.U * max_tok * (D / 4);
-    if (tid >= n) return;
-    const int u = (int)(tid / ((size_t)max_tok * (D / 4)));
-    const int rem = (int)(tid - (size_t)u * max_tok * (D / 4));
-    const int t = rem / (D / 4), ch = rem % (D / 4);
-    const int P = unit_prefill_len(L, in, u);
-    if (t >= min(P, kept_pages(L, P) * L.ps)) return;
-    const size_t src = ((size_t)u * in.stride + t) * D + ch * 4;
-    const size_t dst = ((size_t)u * L.Lcap + t) * D + ch * 4;
-    st4((float*)L.K + dst, ld4(k + src));
-    st4((float*)L.V + dst, ld4(v + src));
-}
-
-// Representative keys of the pinned pages, needed only when they are ranked:
-// per-channel min and max over each page's prefill tokens (Section 3.3). One
-// thread per (unit, page, channel) over max_pages pages per unit; a
-// wavefront reads 64 consecutive channels of one token at a time.
-template <typename T>
-__global__ void k_prefill_rep(LayerView L, const T* __restrict__ k, PrefillIn in, int max_pages) {
-    const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int D = L.D, ps = L.ps;
-    if (tid >= (size_t)L.U * max_pages * D) return;
-    const int c = (int)(tid % D);
-    const size_t up = tid / D;
-    const int pg = (int)(up % max_pages), u = (int)(up / max_pages);
-    const int P = unit_prefill_len(L, in, u);
-    if (pg >= kept_pages(L, P)) return;            // also P < 0; else pg * ps < P
-    const int t0 = pg * ps, t1 = min(P, t0 + ps);
-    const T* ku = k + (size_t)u * in.stride * D + c;
-    T hi = ku[(size_t)t0 * D], lo = hi;
-    for (int t = t0 + 1; t < t1; ++t) {
-        const T x = ku[(size_t)t * D];
-        if (to_f(x) > to_f(hi)) hi = x;
-        if (to_f(x) < to_f(lo)) lo = x;
-    }
-    const size_t o = ((size_t)u * L.S + pg) * D + c;
-    ((T*)L.kmax)[o] = hi;
-    ((T*)L.kmin)[o] = lo;
 }
 
 // ---------------------------------------------------------------------------
@@ -715,14 +782,6 @@ __device__ __forceinline__ void softmax_sum_block(const LayerView& L, double* hb
         s_score[p] = acc;
     }
     __syncthreads();
-}
-
-// Makes this wavefront's LDS writes visible to its own later LDS reads (the
-// lanes of one wavefront exchanging data through LDS; no workgroup barrier).
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Retention policy of one unit, run by one wavefront (Algorithm 1, the
@@ -2305,8 +2364,6 @@ __global__ __launch_bounds__(NW * 64) void k_prompt_select_mfma(LayerView L, Ste
     }
 }
 
-inline unsigned grid1d(size_t n, int block) { return (unsigned)((n + block - 1) / block); }
-
 // LDS of the step kernel: the queries in fp32, the attention wavefronts'
 // partial outputs, the fused epilogue's slot arrays (with the per-head
 // bounds of the softmax aggregation), and a block list
@@ -2601,34 +2658,26 @@ hipError_t launch_prompt_select(const LayerView& L, const StepIO& io, hipStream_
     return hipGetLastError();
 }
 
+template <typename T, int D>
+void launch_prefill_t(const LayerView& L, const void* k, const void* v, const PrefillIn& in, int max_tok,
+                      hipStream_t stream) {
+    const bool reps = L.rank_pinned || L.topk >= 0;
+    const int tile = prefill_tile<T, D>(), tiles = reps ? std::max(1, L.ps / tile) : 1;
+    const int per = kPrefillWaves * tiles * tile;  // tokens of a workgroup
+    const int chunks = std::max(1, (max_tok + per - 1) / per);
+    const dim3 grid((unsigned)((size_t)L.U * chunks)), block(kPrefillWaves * 64);
+    if (reps)
+        hipLaunchKernelGGL((k_prefill<T, D, true>), grid, block, 0, stream, L, (const T*)k, (const T*)v, in, chunks, tiles);
+    else
+        hipLaunchKernelGGL((k_prefill<T, D, false>), grid, block, 0, stream, L, (const T*)k, (const T*)v, in, chunks, tiles);
+}
+
 hipError_t launch_prefill(const LayerView& L, const void* k, const void* v, const PrefillIn& in, int max_tok,
                           hipStream_t stream) {
-    hipLaunchKernelGGL(k_prefill_meta, dim3(L.U), dim3(256), 0, stream, L, in);
-    if (max_tok > 0) {
-        if (L.bf16) {
-            const size_t n = (size_t)L.U * max_tok * (L.D / 8) + (size_t)L.U * ((max_tok + 7) / 8) * L.D;
-            if (L.D == 128)
-                hipLaunchKernelGGL(k_prefill_bf16<128>, dim3(grid1d(n, 256)), dim3(256), 0, stream, L,
-                                   (const uint16_t*)k, (const uint16_t*)v, in, max_tok);
-            else
-                hipLaunchKernelGGL(k_prefill_bf16<64>, dim3(grid1d(n, 256)), dim3(256), 0, stream, L,
-                                   (const uint16_t*)k, (const uint16_t*)v, in, max_tok);
-        } else {
-            const size_t n = (size_t)L.U * max_tok * (L.D / 4);
-            hipLaunchKernelGGL(k_prefill_f32, dim3(grid1d(n, 256)), dim3(256), 0, stream, L, (const float*)k,
-                               (const float*)v, in, max_tok);
-        }
-        if (L.rank_pinned || L.topk >= 0) {
-            const int max_pages = (max_tok + L.ps - 1) / L.ps;
-            const size_t n = (size_t)L.U * max_pages * L.D;
-            if (L.bf16)
-                hipLaunchKernelGGL(k_prefill_rep<uint16_t>, dim3(grid1d(n, 256)), dim3(256), 0, stream, L,
-                                   (const uint16_t*)k, in, max_pages);
-            else
-                hipLaunchKernelGGL(k_prefill_rep<float>, dim3(grid1d(n, 256)), dim3(256), 0, stream, L,
-                                   (const float*)k, in, max_pages);
-        }
-    }
+    if (L.bf16 && L.D == 128) launch_prefill_t<uint16_t, 128>(L, k, v, in, max_tok, stream);
+    else if (L.bf16) launch_prefill_t<uint16_t, 64>(L, k, v, in, max_tok, stream);
+    else if (L.D == 128) launch_prefill_t<float, 128>(L, k, v, in, max_tok, stream);
+    else launch_prefill_t<float, 64>(L, k, v, in, max_tok, stream);
     return hipGetLastError();
 }
 

@@ -69,7 +69,7 @@ struct raas_pool {
     float* pivl = nullptr;        // [2][U][npr] prompt bound intervals (bf16, fewer units than CUs)
     int npr = 0;                  // prompt region's slots (0: none)
     int nt = 0;                   // K/V blocks streamed with non-temporal loads
-    int32_t* seqbuf = nullptr;   // [2][batch] prefill lengths and mask of a ragged prefill
+    int32_t* seqbuf = nullptr;   // [batch] prefill lengths of a ragged prefill of many sequences, -1 where not selected
     int32_t* seqhost = nullptr;  // pinned host staging of seqbuf
     hipEvent_t seq_copied = nullptr;  // recorded after the last staging copy
     size_t bytes = 0;
@@ -426,7 +426,7 @@ raas_status raas_create_pool(const raas_config* cfg, void* stream, raas_pool** o
         {(void**)&p->score,
          (size_t)p->U * p->S * (cfg->score_aggregation == RAAS_SCORE_SOFTMAX_SUM ? p->G : 1) * sizeof(double)},
         {(void**)&p->arrived, 2 * (size_t)p->U * sizeof(int32_t)},
-        {(void**)&p->seqbuf, 2 * (size_t)cfg->batch * sizeof(int32_t)},
+        {(void**)&p->seqbuf, (size_t)cfg->batch * sizeof(int32_t)},
         {(void**)&p->fill_att, p->npr > 0 ? (size_t)p->U * p->S * sizeof(int32_t) : 4},
         {(void**)&p->blist, p->npr > 0 ? (size_t)p->U * (p->Lcap / kBlockTokens) * sizeof(int32_t) : 4},
         {(void**)&p->bcnt, p->npr > 0 ? (size_t)p->U * 2 * sizeof(int32_t) : 4},
@@ -453,7 +453,7 @@ raas_status raas_create_pool(const raas_config* cfg, void* stream, raas_pool** o
             return hip_fail(e, "hipMemsetAsync");
         }
     }
-    hipError_t eh = hipHostMalloc((void**)&p->seqhost, 2 * (size_t)cfg->batch * sizeof(int32_t));
+    hipError_t eh = hipHostMalloc((void**)&p->seqhost, (size_t)cfg->batch * sizeof(int32_t));
     if (eh != hipSuccess) {
         p->seqhost = nullptr;
         raas_destroy(p);
@@ -506,7 +506,8 @@ raas_status raas_prefill(raas_pool* p, int32_t layer, const void* k, const void*
         keep = pcap;
     }
     hipStream_t s = (hipStream_t)stream;
-    const PrefillIn in{nullptr, nullptr, prefill_len, prefill_len};
+    PrefillIn in{};
+    in.P = in.stride = prefill_len;
     hipError_t e = launch_prefill(view(p, layer), k, v, in, std::min(prefill_len, keep * p->ps), s);
     if (e != hipSuccess) return hip_fail(e, "prefill launch");
     p->prefilled[layer] = 1;
@@ -543,28 +544,35 @@ raas_status raas_prefill_ragged(raas_pool* p, int32_t layer, const void* k, cons
         return fail(RAAS_E_STATE, "the first prefill of layer %d must cover every sequence", layer);
     if (max_tok > 0 && (!k || !v)) return fail(RAAS_E_INVALID, "k or v is NULL");
     hipStream_t s = (hipStream_t)stream;
-    // lengths and mask go to the device through the pool's pinned staging
-    // buffer, once the previous ragged prefill's copy out of it has run
+    // The lengths travel as kernel arguments; for more sequences than those
+    // hold, through the pool's pinned staging buffer, once the previous ragged
+    // prefill's copy out of it has run (the copy ahead of the kernel and its
+    // event cost 9 us of a 50 us admission of 32 sequences).
+    PrefillIn in{};
+    in.P = -1;
+    in.stride = max_len;
+    auto length = [&](int b) { return seq_mask && !seq_mask[b] ? -1 : prefill_lens[b]; };
     hipError_t e = hipSuccess;
-    if (!p->seq_copied) {
-        e = hipEventCreateWithFlags(&p->seq_copied, hipEventDisableTiming);
-        if (e != hipSuccess) {
-            p->seq_copied = nullptr;
-            return hip_fail(e, "hipEventCreateWithFlags");
-        }
+    if (B <= kArgSeqs) {
+        for (int b = 0; b < B; ++b) in.arg_lens[b] = length(b);
     } else {
-        e = hipEventSynchronize(p->seq_copied);
-        if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize");
+        if (!p->seq_copied) {
+            e = hipEventCreateWithFlags(&p->seq_copied, hipEventDisableTiming);
+            if (e != hipSuccess) {
+                p->seq_copied = nullptr;
+                return hip_fail(e, "hipEventCreateWithFlags");
+            }
+        } else {
+            e = hipEventSynchronize(p->seq_copied);
+            if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize");
+        }
+        for (int b = 0; b < B; ++b) p->seqhost[b] = length(b);
+        e = hipMemcpyAsync(p->seqbuf, p->seqhost, (size_t)B * sizeof(int32_t), hipMemcpyHostToDevice, s);
+        if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
+        e = hipEventRecord(p->seq_copied, s);
+        if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
+        in.lens = p->seqbuf;
     }
-    for (int b = 0; b < B; ++b) {
-        p->seqhost[b] = prefill_lens[b];
-        p->seqhost[(size_t)B + b] = (seq_mask && !seq_mask[b]) ? 0 : 1;
-    }
-    e = hipMemcpyAsync(p->seqbuf, p->seqhost, 2 * (size_t)B * sizeof(int32_t), hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
-    e = hipEventRecord(p->seq_copied, s);
-    if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
-    const PrefillIn in{p->seqbuf, p->seqbuf + B, 0, max_len};
     e = launch_prefill(view(p, layer), k, v, in, max_tok, s);
     if (e != hipSuccess) return hip_fail(e, "prefill launch");
     if (!p->prefilled[layer]) {

@@ -582,6 +582,69 @@ def test_f32_blocks(case):
     assert rep.evictions > 0
 
 
+# The prefill store at the edges of its tiles (16 to 64 tokens, four to a
+# workgroup) and of pages shorter and longer than a tile, with the pinned
+# pages' representative keys in use (ranked, or a prompt region selected from).
+PREFILL_CASES = [
+    dict(page_size=8, prefill_len=127, rank_pinned=True),
+    dict(page_size=16, prefill_len=129, rank_pinned=True),
+    dict(page_size=64, prefill_len=257, rank_pinned=True),
+    dict(page_size=128, prefill_len=500, rank_pinned=True),
+    dict(page_size=32, prefill_len=33, head_dim=64, rank_pinned=True),
+    dict(page_size=128, prefill_len=511, head_dim=64, rank_pinned=True),
+    dict(page_size=8, prefill_len=65, dtype="f32", rank_pinned=True),
+    dict(page_size=32, prefill_len=130, dtype="f32", rank_pinned=True),
+    dict(page_size=64, prefill_len=255, dtype="f32", head_dim=64, rank_pinned=True),
+    dict(page_size=16, prefill_len=383, prompt_tokens=384, prompt_topk=5),
+    dict(page_size=64, prefill_len=600, prompt_tokens=512, prompt_topk=3),
+]
+
+
+@pytest.mark.parametrize("case", PREFILL_CASES, ids=[",".join("%s=%s" % kv for kv in c.items()) for c in PREFILL_CASES])
+def test_prefill_tiles(case):
+    case = dict(case)
+    run_kw = {k: case.pop(k) for k in ("rank_pinned", "prompt_tokens", "prompt_topk") if k in case}
+    ps = case["page_size"]
+    budget = 4 * ps if "prompt_tokens" in run_kw else (case["prefill_len"] + ps - 1) // ps * ps + 4 * ps
+    w = small(budget=budget, decode_steps=6 * ps, **case)
+    _say("case prefill tiles %s %s" % (case, run_kw))
+    rep = run_parity(w, seed=29, steps=w.decode_steps, **run_kw)
+    _report(rep, "prefill-tiles")
+    assert rep.evictions > 0
+
+
+@pytest.mark.parametrize("batch", [3, 256, 257])
+def test_ragged_prefill_lengths(batch):
+    """Per-sequence lengths in the kernel's arguments (up to 256 sequences) or
+    through the pool's buffer, with a second prefill of chosen sequences: the
+    next step's outputs against attention over each sequence's own prompt in
+    64 bits. The bound is the bf16 one of the parity runs."""
+    import torch
+    import paper_2502_11147_amd as raas
+
+    _say("case ragged prefill lengths batch %d" % batch)
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    rng = np.random.default_rng(batch)
+    G, d, most = 2, 64, 150
+    pool = raas.Pool(batch, 1, G, 1, d, 16, 256)
+    rand = lambda *shape: torch.randn(*shape, generator=g, device="cuda").bfloat16()
+    kv = [rand(batch, 1, most, d) for _ in range(4)]
+    lens, lens2 = rng.integers(0, most + 1, batch), rng.integers(0, most + 1, batch)
+    mask = rng.integers(0, 2, batch)
+    q, kn, vn = rand(batch, G, d), rand(batch, 1, d), rand(batch, 1, d)
+    out = torch.empty_like(q)
+    pool.prefill_ragged(0, kv[0], kv[1], lens)
+    pool.prefill_ragged(0, kv[2], kv[3], lens2, mask=mask)
+    pool.decode_step(0, q, kn, vn, out)
+    for b in range(batch):
+        K, V, P = (kv[2], kv[3], lens2[b]) if mask[b] else (kv[0], kv[1], lens[b])
+        K = torch.cat([K[b, 0, :P], kn[b]]).double()
+        V = torch.cat([V[b, 0, :P], vn[b]]).double()
+        ref = torch.softmax(q[b].double() @ K.T.contiguous() / d ** 0.5, 1) @ V
+        assert (out[b].double() - ref).abs().max() <= 2e-2, (b, P)
+    pool.close()
+
+
 # One page table per (sequence, layer) shared by its KV heads (decision
 # scope 1), against the oracle's grouped step; (aggregation, rank_pinned).
 SCOPE_VARIANTS = [(0, False), (1, False), (0, True)]
