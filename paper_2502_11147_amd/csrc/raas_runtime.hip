@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <new>
 #include <string>
@@ -68,7 +69,9 @@ struct raas_pool {
     int32_t* bcnt = nullptr;      // [U][2]
     float* pivl = nullptr;        // [2][U][npr] prompt bound intervals (bf16, fewer units than CUs)
     int npr = 0;                  // prompt region's slots (0: none)
-    int nt = 0;                   // K/V blocks streamed with non-temporal loads
+    int device = 0;
+    // g_streamed after each layer's last step; 0: no step yet
+    std::vector<unsigned long long> streamed_at;
     int32_t* seqbuf = nullptr;   // [batch] prefill lengths of a ragged prefill of many sequences, -1 where not selected
     int32_t* seqhost = nullptr;  // pinned host staging of seqbuf
     hipEvent_t seq_copied = nullptr;  // recorded after the last staging copy
@@ -145,7 +148,7 @@ LayerView view(const raas_pool* p, int layer) {
     L.pivl = p->pivl;
     L.pchunk = 0;
     L.lcap_blk = p->Lcap / kBlockTokens;
-    L.nt = p->nt;
+    L.nt = 0;
     L.det = p->cfg.deterministic;
     L.early = 0;
     return L;
@@ -278,6 +281,30 @@ raas_status static_scratch(void** out) {
 
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
+// Bytes of keys and values that this process's steps have read, per device
+// (a hint: it chooses between two kinds of load and no result depends on it).
+std::atomic<unsigned long long> g_streamed[kMaxDevices];
+
+// Whether a step that reads `own` bytes of its layer reads them with
+// non-temporal loads. Steps of a layer read its pool in alternating
+// directions, so what the memory-side cache (256 MB) still holds of it is the
+// cache less what other layers and pools have streamed since; when that is
+// less than two thirds of the layer, non-temporal loads are the faster ones,
+// which leave the cache alone (us per step, ordinary / non-temporal: 268 MB
+// alone 41.2 / 45.2, with one more pool of that size in between 52.8 / 46.8;
+// 104 MB with 104, 208 and 312 MB in between 20.6 / 22.3, 23.4 / 22.9 and 25.8
+// / 23.2; 138 MB with 138 and 276 MB in between 28.1 / 30.9 and 34.7 / 31.2;
+// 335 MB alone 62.4 / 65.9, 402 MB alone 69.9 / 68.0). A layer's first step counts the pool's other
+// layers; a deterministic pool always does, so that its instance, and with it
+// the rounding, depends on nothing outside it.
+bool non_temporal(raas_pool* p, int layer, double own) {
+    const unsigned long long before = p->streamed_at[layer], now = g_streamed[p->device].fetch_add(
+        (unsigned long long)own, std::memory_order_relaxed);
+    const double others = before == 0 || p->cfg.deterministic ? (p->cfg.n_layers - 1.0) * own : (double)(now - before);
+    p->streamed_at[layer] = now + (unsigned long long)own;
+    return others + own * 2.0 / 3.0 > 256e6;
+}
+
 // One decode step of one layer (raas_decode_step_masked); with
 // fixed_scratch the per-step scratch comes from `scratch` instead of the
 // pool's buffers, and nothing is allocated or profiled.
@@ -343,6 +370,8 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
     // step starts with the blocks the previous one read last, the likeliest
     // to be still in the GPU's memory-side cache.
     L.rev = p->descending[layer];
+    // keys and values of the blocks the step attends, and the prompt pages' representative keys
+    L.nt = non_temporal(p, layer, 2.0 * p->U * p->D * p->esz * ((double)work_blocks * kBlockTokens + p->npr));
     const bool prof = !fixed_scratch;
 
     if (select_kernel) {  // Quest on the prompt: which prompt pages this step attends to
@@ -387,6 +416,8 @@ raas_status raas_create_pool(const raas_config* cfg, void* stream, raas_pool** o
     raas_pool* p = new (std::nothrow) raas_pool();
     if (!p) return fail(RAAS_E_OOM, "host allocation failed");
     p->cfg = *cfg;
+    (void)hipGetDevice(&p->device);
+    if (p->device < 0 || p->device >= kMaxDevices) p->device = 0;  // (only picks a counter)
     p->U = cfg->batch * cfg->n_kv_heads;
     p->G = cfg->n_q_heads / cfg->n_kv_heads;
     p->D = cfg->head_dim;
@@ -402,12 +433,7 @@ raas_status raas_create_pool(const raas_config* cfg, void* stream, raas_pool** o
     p->keep_max.assign((size_t)cfg->n_layers, 0);
     p->steps.assign((size_t)cfg->n_layers, 0);
     p->descending.assign((size_t)cfg->n_layers, 0);
-    // A step reads a layer's whole pool; the same layer comes round again
-    // after every layer's pool has been read. When all of them exceed twice
-    // the memory-side cache (256 MB), nothing of a step's reads is left there
-    // for the next: the blocks are then read with non-temporal loads, which
-    // stream faster. Smaller pools keep ordinary loads and the cache's reuse.
-    p->nt = 2.0 * (double)cfg->n_layers * p->U * p->Lcap * p->D * p->esz > 2.0 * 256e6 ? 1 : 0;
+    p->streamed_at.assign((size_t)cfg->n_layers, 0);
     const size_t Ly = (size_t)cfg->n_layers;
     const int nblk = p->Lcap / kBlockTokens;
     const int max_split = nblk < kMaxSplits ? nblk : kMaxSplits;
