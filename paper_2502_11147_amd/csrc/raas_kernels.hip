@@ -402,6 +402,44 @@ __device__ __forceinline__ double dpp_f64(double x) {
     const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
+// lanes i ^ 16 and i ^ 32 of a double (each half by a permlane swap; swap16
+// and swap32 return both sides, which the caller combines)
+__device__ __forceinline__ double2 swap16_f64(double x) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    return make_double2(__builtin_bit_cast(double, ((unsigned long long)(unsigned)hi[0] << 32) | (unsigned)lo[0]),
+                        __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi[1] << 32) | (unsigned)lo[1]));
+}
+__device__ __forceinline__ double2 swap32_f64(double x) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    return make_double2(__builtin_bit_cast(double, ((unsigned long long)(unsigned)hi[0] << 32) | (unsigned)lo[0]),
+                        __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi[1] << 32) | (unsigned)lo[1]));
+}
+// Whole-wavefront maximum and sum of a double, the result on every lane, in
+// the same order on each: quads (xor 1, xor 2), the mirrors within 8 and 16
+// lanes (the lanes of a quad, then of a half, hold equal values by then), and
+// the two swaps.
+__device__ __forceinline__ double wave_max_f64(double x) {
+    x = fmax(x, dpp_f64<0xB1>(x));
+    x = fmax(x, dpp_f64<0x4E>(x));
+    x = fmax(x, dpp_f64<0x141>(x));
+    x = fmax(x, dpp_f64<0x140>(x));
+    const double2 a = swap16_f64(x);
+    const double2 b = swap32_f64(fmax(a.x, a.y));
+    return fmax(b.x, b.y);
+}
+__device__ __forceinline__ double wave_sum_f64(double x) {
+    x += dpp_f64<0xB1>(x);
+    x += dpp_f64<0x4E>(x);
+    x += dpp_f64<0x141>(x);
+    x += dpp_f64<0x140>(x);
+    const double2 a = swap16_f64(x);
+    const double2 b = swap32_f64(a.x + a.y);
+    return b.x + b.y;
+}
 __device__ __forceinline__ float max_xor16_32(float x) {
     const unsigned u = __builtin_bit_cast(unsigned, x);
     const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
@@ -753,8 +791,7 @@ __device__ __forceinline__ void softmax_sum_block(const LayerView& L, double* hb
         double mx = -INFINITY;
         for (int p = lane; p < S; p += 64)
             if (ranked(L, s_state[p])) mx = fmax(mx, bound(hbj + (size_t)p * G));
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
+        mx = wave_max_f64(mx);
         double z = 0.0;
         for (int p = lane; p < S; p += 64)
             if (ranked(L, s_state[p])) {
@@ -762,8 +799,7 @@ __device__ __forceinline__ void softmax_sum_block(const LayerView& L, double* hb
                 if (!PUB) hbj[(size_t)p * G] = e;
                 z += e;
             }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) z += __shfl_xor(z, off);
+        z = wave_sum_f64(z);
         if (lane == 0) {
             s_mz[2 * hj] = mx;
             s_mz[2 * hj + 1] = z;
@@ -1276,7 +1312,15 @@ __device__ __forceinline__ void finish_units(const LayerView& L, const StepIO& i
         if (merge) merge_out<T>(L, io, u0, mf, s_ml, tid, nth);
     });
     __syncthreads();
-    for (int uh = 0; uh < nu; ++uh) retention_store(L, io, u0 + uh, ur, s_state, s_ts, s_lid, ret, tid, nth);
+    // the units side by side, each by an equal share of the threads
+    int per = nth, share = 0, shares = 1;
+    if (nu > 1) {
+        per = max(1, nth / nu);
+        share = tid / per;
+        shares = nth / per;
+    }
+    for (int uh = share; uh < nu && share < shares; uh += shares)
+        retention_store(L, io, u0 + uh, ur, s_state, s_ts, s_lid, ret, tid - share * per, per);
 }
 
 // One 32-token block of attention for the GQA group held by this wavefront:
@@ -2028,7 +2072,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
         // the sequence decides.
         __shared__ int s_last, s_aux[261];
         const int nu = L.hgrp;
-        if (!arrive_last(L.arrived + u, nsplit, &s_last)) return;
+        if ((nsplit > 1 || nu == 1) && !arrive_last(L.arrived + u, nsplit, &s_last)) return;
         if (nu > 1 && nsplit > 1) {
             const MergeFirst mf = merge_first(L, u, tid);
             merge_stage(L, u, mf, reinterpret_cast<float*>(smem), tid, NW * 64);
