@@ -337,8 +337,13 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
     // the retention come a block sooner, which pays where a workgroup of 8
     // wavefronts streams at least 8 blocks each (batch 32 at L 2048: 40.79 ->
     // 40.38 us, the Qwen stack and L 8192 level) and not below (batch 1 at
-    // L 1024 +0.14 us; batch 128 at L 512, 2 wavefronts, +0.23 us)
-    L.early = pl.waves == 8 && (pl.nsplit > 1 || L.nblk * (L.bf16 ? 1 : 2) >= 8 * pl.waves) ? 1 : 0;
+    // L 1024 +0.11 us; batch 128 at L 512, 2 wavefronts, +0.23 us), but where
+    // blocks are half as long (head_dim 64: the one-unit fp32 pool 9.65 ->
+    // 9.37 us, 32 x 2 units at L 1024 bf16 11.81 -> 11.47) and in a split
+    // unit, whose scores the last workgroup waits for (64 units, L 1536: 20.6
+    // -> 19.6 us)
+    L.early =
+        pl.waves == 8 && (L.D == 64 || pl.nsplit > 1 || L.nblk * (L.bf16 ? 1 : 2) >= 8 * pl.waves) ? 1 : 0;
     const bool select_kernel = p->npr > 0 && !pl.select_in_step;
     if (fixed_scratch) {
         const size_t U = (size_t)p->U, S = (size_t)p->S;

@@ -118,3 +118,57 @@ def test_static_scratch_refuses_oversized_step():
     pool.decode_step(0, q, kv, kv, out)  # the pool's own scratch still serves it
     assert np.all(pool.export_state(0)["clock"] == 2001)
     pool.close()
+
+
+@pytest.mark.parametrize("kw,splits,opt", [(dict(budget=512), 4, {}), (dict(budget=512), 4, dict(scope=1)),
+                                           (dict(budget=256, dtype="f32"), 3, {}), (dict(budget=256), None, {})],
+                         ids=["split", "sequence", "f32-split", "fused"])
+def test_graph_replays(kw, splits, opt):
+    """A captured static step replayed with new inputs against eager steps of
+    a second pool: the arrival counters of split units and shared decisions
+    are back at zero after every replay, with eager work of the program in
+    between. Retention bit for bit, outputs within the parity bounds."""
+    import torch
+
+    w = _w(batch=3, prefill_len=60, **kw)
+    B, Hq, Hkv, d, S = w.batch, w.n_q_heads, w.n_kv_heads, w.head_dim, w.slots
+    dt = torch.bfloat16 if w.dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rand = lambda *shape: torch.randn(*shape, generator=g, device="cuda").to(dt)
+    pools = [new_pool(w, splits, **opt) for _ in range(2)]
+    k0, v0 = rand(B, Hkv, 60, d), rand(B, Hkv, 60, d)
+    bufs = [dict(out=torch.zeros(B, Hq, d, dtype=dt, device="cuda"),
+                 page_table=torch.zeros(B, Hkv, S, dtype=torch.int32, device="cuda"),
+                 timestamps=torch.zeros(B, Hkv, S, dtype=torch.int32, device="cuda"),
+                 evicted=torch.zeros(B, Hkv, dtype=torch.int32, device="cuda")) for _ in pools]
+    q, k, v = rand(B, Hq, d), rand(B, Hkv, d), rand(B, Hkv, d)
+    step = lambda i: pools[i].decode_step_static(0, q, k, v, **bufs[i])
+
+    def new_inputs():
+        for x in (q, k, v):
+            x.copy_(rand(*x.shape))
+
+    for p in pools:
+        p.prefill(0, k0, v0)
+    for _ in range(w.budget - 60 + 2 * w.page_size):
+        new_inputs()
+        step(0)
+        step(1)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step(0)
+    for i in range(3 * w.page_size):
+        new_inputs()
+        graph.replay()
+        step(1)
+        if i % 5 == 0:
+            torch.cuda.synchronize()
+        a, b = bufs
+        for name in ("page_table", "timestamps", "evicted"):
+            assert torch.equal(a[name], b[name]), (i, name)
+        tol = 2e-2 if dt == torch.bfloat16 else 2e-5
+        assert (a["out"].float() - b["out"].float()).abs().max() <= tol, i
+    say("case graph replays %s %s %s" % (kw, splits, opt))
+    for p in pools:
+        p.close()
