@@ -511,8 +511,8 @@ def main():
     run(fill, args.warmup)
     torch.cuda.synchronize()
 
-    # one kernel per step (the step kernel runs the epilogue and, with a
-    # prompt region, the selection) or more?
+    # one kernel per step (the step kernel chooses the prompt pages too) or a
+    # selection kernel in front?
     pool.profile((1 << KERNEL_EPILOGUE) | (1 << KERNEL_SELECT))
     run(fill + args.warmup, 1)
     fused = pool.profile_read(KERNEL_EPILOGUE)[1] == 0
@@ -537,7 +537,7 @@ def main():
         res = resident_schedule(st, w.page_size, S, args.steps)
 
     # timed region: HIP events on the launch stream (torch's current stream)
-    # around all K steps; with two kernels per step, the library also times
+    # around all K steps; with a selection kernel, the library also times
     # each kernel on every 16th step
     ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
@@ -567,17 +567,13 @@ def main():
     # it is the only kernel of the step, else the sampled per-kernel events
     step_avg_s = span_ms / 1e3 / (args.steps * nl) if alone else step_ms / 1e3 / max(step_n, 1)
     step_b = float(np.mean(step_bytes(w, res, (n_ev0 + n_pin)[None, :], S)))
-    # bytes of the step kernel alone: everything but what the epilogue kernel moves
-    e = 2 if w.dtype == "bf16" else 4
-    kernel_b = step_b if fused else step_b - U * w.group * w.head_dim * e - 24 * U * S
+    kernel_b = step_b
     achieved = kernel_b / step_avg_s / 1e9
-    kname = "k_step_bf16" if w.dtype == "bf16" else ("k_step_f32_fused" if fused else "k_step_f32")
+    kname = "k_step_bf16" if w.dtype == "bf16" else "k_step_f32"
     if variant:
         traffic, traffic_src = None, "no stored counter profile for the variants"
-    elif fused:
-        traffic, traffic_src = stored_traffic(kname, w.name)
     else:
-        traffic, traffic_src = None, "two kernels per step"
+        traffic, traffic_src = stored_traffic(kname, w.name)
     line = {
         "metric": "decode tokens/s per GPU at batch B, budget L; achieved HBM GB/s vs peak",
         "value": round(tokens_per_s, 1),
@@ -605,7 +601,7 @@ def main():
         },
         "step_hbm_gbs_algorithmic": round(step_b * nl / (elapsed / args.steps) / 1e9, 1),
         "roofline": {
-            "kernel": kname + ("" if fused else " (+k_epilogue)"),
+            "kernel": kname,
             "bound": "hbm",
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS,

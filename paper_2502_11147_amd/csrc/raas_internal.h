@@ -91,14 +91,14 @@ struct StepIO {
 struct StepPlan {
     int waves;       // wavefronts per step workgroup (bf16)
     int nsplit, bps; // splits per unit and blocks per split
-    bool fused;      // true: the step workgroup also runs the epilogue (nsplit == 1, bf16)
+    bool fused;      // true: one workgroup per unit, which decides by itself
     bool select_in_step;  // true: the step kernel chooses the prompt pages (no selection kernel)
     size_t lds;      // dynamic LDS of the step kernel
 };
 
 // work_blocks: 32-token blocks a unit's step attends (Lcap / 32 less the
 // unchosen prompt blocks); grouped: retention decided per group of units, by
-// the epilogue kernel;
+// the group's last workgroup;
 // list_ints: LDS ints of a block list or of the in-step prompt selection (0
 // without a prompt region); fixed_scratch: raas_decode_step_static
 StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool bf16, int agg,
@@ -113,7 +113,7 @@ hipError_t allow_large_lds();
 // max_tok: the most tokens any selected unit keeps (min(P, kept pages * ps)).
 hipError_t launch_prefill(const LayerView& L, const void* k, const void* v, const PrefillIn& in, int max_tok,
                           hipStream_t stream);
-// The step kernel: the whole step (bf16 and fused fp32 plans), or attention, page scores and append.
+// The step kernel: the whole step of every unit.
 hipError_t launch_step(const LayerView& L, const StepIO& io, const StepPlan& plan, double r,
                        hipStream_t stream);
 

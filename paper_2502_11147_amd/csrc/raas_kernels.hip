@@ -16,10 +16,10 @@
 //
 // One decode step is one launch of a step kernel (attention over the
 // resident pages with the new token substituted in registers, the append of
-// that token, the page scores) whose workgroup, when one workgroup covers a
-// whole unit, also runs the epilogue (top-r refresh, eviction, next target
-// slot, state out). When a unit is split over several workgroups, or the pool
-// is fp32, the epilogue is a second kernel that also merges the splits.
+// that token, the page scores, the top-r refresh, the eviction, the next
+// target slot, the state out). When a unit is split over several workgroups,
+// or units decide together, the last of these workgroups to end merges,
+// decides and writes the state.
 #include <math.h>
 
 #include <algorithm>
@@ -1750,7 +1750,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
     if constexpr (LM != 2) {
         if (real(b)) f_next = (w < nown) ? (slot_first < S ? (slot_first == ns ? nf + 1 : fill_first) : 0) : row_fill(b);
 
-        // staging for the scores and the epilogue
+        // staging for the scores and the retention
         if (tid < G * D) s_qf[qpad_index<D>(tid)] = to_f(q_first);
         for (int i = tid + NW * 64; i < G * D; i += NW * 64) s_qf[qpad_index<D>(i)] = to_f(qg[i]);
         if (tid < D / VE) {
@@ -2409,7 +2409,7 @@ __global__ __launch_bounds__(NW * 64) void k_prompt_select_mfma(LayerView L, Ste
 }
 
 // LDS of the step kernel: the queries in fp32, the attention wavefronts'
-// partial outputs, the fused epilogue's slot arrays (with the per-head
+// partial outputs, the fused retention's slot arrays (with the per-head
 // bounds of the softmax aggregation), and a block list
 size_t step_lds(int G, int D, int S, int NW, bool fused, int agg, int list_ints) {
     size_t b = (size_t)4 * G * qpad_row(D) + (size_t)NW * G * (D + 4) * 4;
