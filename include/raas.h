@@ -204,12 +204,13 @@ raas_status raas_decode_step_masked(raas_pool* pool, int32_t layer, const void* 
  * lists -- lies
  * in a fixed array of RAAS_STATIC_SCRATCH_BYTES in the library's device
  * code instead of the pool's own buffers. The call allocates nothing and
- * records no profiling events. Steps whose plan needs no scratch (one
- * workgroup per unit without a separate prompt selection, the default for
- * bf16 pools of up to 48 blocks per unit or batches that fill the GPU)
- * never touch the array. A step needing more than the array holds is
- * refused with RAAS_E_INVALID, before anything is enqueued. Each GPU holds
- * one copy of the array until the process ends, shared by every call on it:
+ * records no profiling events. Steps without a separate prompt selection
+ * never touch the array when one workgroup covers a unit (the default for
+ * batches that fill the GPU) or when the plan splits units of at most 48
+ * blocks (of 32 tokens in a bf16 pool, 16 in an fp32 one), whose partials and
+ * scores stay in the pool's own buffers. A step needing more than the array
+ * holds is refused with RAAS_E_INVALID, before anything is enqueued. Each GPU
+ * holds one copy of the array until the process ends, shared by every call on it:
  * its contents are the last call's (no step relies on it starting at zero),
  * and calls that overlap on one GPU (other streams, other threads) race on
  * it, so they must be ordered. Errors as raas_decode_step. */

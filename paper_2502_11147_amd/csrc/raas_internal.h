@@ -93,6 +93,7 @@ struct StepPlan {
     int nsplit, bps; // splits per unit and blocks per split
     bool fused;      // true: one workgroup per unit, which decides by itself
     bool select_in_step;  // true: the step kernel chooses the prompt pages (no selection kernel)
+    bool pool_scratch;    // true: raas_decode_step_static, too, keeps partials and scores in the pool's buffers
     size_t lds;      // dynamic LDS of the step kernel
 };
 
@@ -100,10 +101,10 @@ struct StepPlan {
 // unchosen prompt blocks); grouped: retention decided per group of units, by
 // the group's last workgroup;
 // list_ints: LDS ints of a block list or of the in-step prompt selection (0
-// without a prompt region); fixed_scratch: raas_decode_step_static
+// without a prompt region)
 StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool bf16, int agg,
                    bool grouped, int list_ints, int split_override,
-                   int npr, int nkv, bool fixed_scratch);
+                   int npr, int nkv);
 // Quest on the prompt pages: the attended fills and the block list of a step.
 hipError_t launch_prompt_select(const LayerView& L, const StepIO& io, hipStream_t stream);
 // Lets the step kernels use more than the default dynamic LDS.

@@ -2553,11 +2553,12 @@ constexpr int kFusedBlocks = 32;
 constexpr int kHalfUnits = 113;
 constexpr int kFusedBlocksHalf = 64;
 constexpr int kSplits = 16;
-// Steps whose scratch is the fixed array (raas_decode_step_static) keep the
-// plans that need none up to this many blocks per wavefront, or, in pools of
-// at most kFewSlots slots, kFusedBlocksPerWaveFewSlots.
-constexpr int kFusedBlocksPerWave = 6;
-constexpr int kFusedBlocksPerWaveFewSlots = 8;
+// Up to this many blocks per wavefront (in pools of at most kFewSlots slots,
+// kFewSlotsBlocksPerWave) raas_decode_step_static leaves its fixed array alone:
+// such a unit's split keeps its scratch in the pool's buffers, so that these
+// steps may overlap other pools' as they may in one workgroup.
+constexpr int kSmallBlocksPerWave = 6;
+constexpr int kFewSlotsBlocksPerWave = 8;
 constexpr int kFewSlots = 64;
 // With a prompt region and fewer units than CUs, fused up to this many
 // attended blocks per wavefront and prompt pages (batch 1 and 8, 128 prompt
@@ -2576,8 +2577,7 @@ constexpr int kSmallWorkUnits = 1024;
 constexpr int kSmallWorkBlocks = 32;
 
 StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool bf16, int agg,
-                   bool grouped, int list_ints, int split_override, int npr, int nkv,
-                   bool fixed_scratch) {
+                   bool grouped, int list_ints, int split_override, int npr, int nkv) {
     StepPlan pl{};
     const int nblk = Lcap / kBlockTokens;
     // blocks of 16 KB (head_dim 128): 32 tokens in bf16, 16 in fp32
@@ -2607,10 +2607,6 @@ StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool b
     const int fused_blocks = (U < kHalfUnits ? kFusedBlocks : kFusedBlocksHalf) / (bf16 ? 1 : 2);
     if (split_override > 0) {
         want = split_override;
-    } else if (fits && fixed_scratch &&
-               (blocks <= kFusedBlocksPerWave * pl.waves ||
-                (S <= kFewSlots && blocks <= kFusedBlocksPerWaveFewSlots * pl.waves))) {
-        want = 1;
     } else if (fits && bf16 && list_ints > 0 && !agg && U < 256 && npr <= kFusedPromptPages &&
                work <= kFusedPromptBlocksPerWave * pl.waves) {
         // a short prompt region: the fused workgroup chooses its prompt
@@ -2632,6 +2628,9 @@ StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool b
     const bool long_prompt = bf16 && list_ints > 0 && !agg && U < 256 && npr > kFusedPromptPages;
     pl.fused = !grouped && !long_prompt && pl.nsplit == 1 &&
                step_lds(G, D, S, pl.waves, true, agg, list_ints) <= kMaxLds;
+    pl.pool_scratch = fits && split_override <= 0 &&
+                      (blocks <= kSmallBlocksPerWave * pl.waves ||
+                       (S <= kFewSlots && blocks <= kFewSlotsBlocksPerWave * pl.waves));
     pl.lds = step_lds(G, D, S, pl.waves, pl.fused, agg, list_ints);
     // (the workgroup that finishes a split unit reuses the step's LDS)
     if (!pl.fused) pl.lds = std::max(pl.lds, finish_lds(G, S, pl.nsplit, agg, grouped ? nkv : 1));

@@ -330,7 +330,7 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
     const StepPlan pl = plan_step(p->U, p->G, p->D, p->S, L.nblk * kBlockTokens, work_blocks,
                                   p->cfg.dtype == RAAS_BF16, p->cfg.score_aggregation,
                                   p->cfg.decision_scope == RAAS_SCOPE_SEQUENCE, list_ints(p), p->split_override, p->npr,
-                                  p->cfg.n_kv_heads, fixed_scratch);
+                                  p->cfg.n_kv_heads);
     L.nsplit = pl.nsplit;
     L.bps = pl.bps;
     // the first score pass issued with the first blocks: the score barrier and
@@ -347,9 +347,10 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
     const bool select_kernel = p->npr > 0 && !pl.select_in_step;
     if (fixed_scratch) {
         const size_t U = (size_t)p->U, S = (size_t)p->S;
-        const size_t part = pl.fused ? 0 : align256(U * pl.nsplit * p->G * (p->D + 2) * sizeof(float));
+        const bool none = pl.fused || pl.pool_scratch;
+        const size_t part = none ? 0 : align256(U * pl.nsplit * p->G * (p->D + 2) * sizeof(float));
         const size_t score =
-            pl.fused ? 0 : align256(U * S * (p->cfg.score_aggregation == RAAS_SCORE_SOFTMAX_SUM ? p->G : 1) * 8);
+            none ? 0 : align256(U * S * (p->cfg.score_aggregation == RAAS_SCORE_SOFTMAX_SUM ? p->G : 1) * 8);
         const size_t fatt = select_kernel ? align256(U * S * 4) : 0;
         const size_t blist = select_kernel ? align256(U * (p->Lcap / kBlockTokens) * 4) : 0;
         const size_t bcnt = select_kernel ? align256(U * 2 * 4) : 0;
@@ -362,8 +363,10 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
             st = static_scratch(&base);
             if (st != RAAS_OK) return st;
             char* c = (char*)base;
-            L.part = part ? (float*)c : nullptr;
-            L.score = score ? (double*)(c + part) : nullptr;
+            if (!none) {
+                L.part = (float*)c;
+                L.score = (double*)(c + part);
+            }
             if (select_kernel) {
                 L.fill_att = (int32_t*)(c + part + score);
                 L.blist = (int32_t*)(c + part + score + fatt);

@@ -98,6 +98,35 @@ def test_static_scratch_matches_decode_step():
         assert rep.evictions > 0
 
 
+@pytest.mark.parametrize("kw,splits", [
+    (dict(batch=4, budget=1280), None),                              # 8 units of 40 blocks
+    (dict(batch=4, budget=1792, page_size=64), None),                # 56 blocks, 28 slots
+    (dict(batch=3, budget=512, dtype="f32", head_dim=64), None),     # 32 blocks of 16 tokens
+    (dict(batch=3, budget=512, dtype="f32"), 3),                     # forced: scratch in the array
+], ids=["bf16", "few-slots", "f32", "f32-array"])
+def test_static_rounds_as_decode_step(kw, splits):
+    """One plan for both entry points: with the deterministic option a static
+    step's outputs equal an ordinary one's bit for bit, also where the plan
+    splits units that one workgroup could cover."""
+    import torch
+
+    w = _w(prefill_len=kw["budget"] - 100, decode_steps=140, **kw)
+    say("case static rounding %s splits %s" % (kw, splits))
+    pools = [new_pool(w, splits, deterministic=True) for _ in range(2)]
+    K, V = synth.prefill(w, 3, 0)
+    for pool in pools:
+        pool.prefill(0, to_device(K, w.dtype), to_device(V, w.dtype))
+    dt = torch.bfloat16 if w.dtype == "bf16" else torch.float32
+    qd, kd, vd = (to_device(x, w.dtype) for x in synth.steps(w, 3, 0, 0, w.decode_steps))
+    for t in range(w.decode_steps):
+        outs, states = _step_both(*pools, w, qd[t], kd[t], vd[t], w.slots, dt)
+        assert torch.equal(*outs), t
+        for x, y in zip(*states):
+            assert torch.equal(x, y), t
+    for pool in pools:
+        pool.close()
+
+
 def test_static_scratch_refuses_oversized_step():
     import torch
 
