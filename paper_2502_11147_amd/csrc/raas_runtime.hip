@@ -281,9 +281,17 @@ raas_status static_scratch(void** out) {
 
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
-// Bytes of keys and values that this process's steps have read, per device
-// (a hint: it chooses between two kinds of load and no result depends on it).
+// Bytes of keys and values that this process's steps have read, per device: a
+// hint that chooses between two kinds of load. Both read the same values; their
+// kernel instances may round an output differently, as the dynamic claims do.
 std::atomic<unsigned long long> g_streamed[kMaxDevices];
+
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (s == nullptr) return false;  // (the legacy stream cannot be captured)
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
+    return st != hipStreamCaptureStatusNone;
+}
 
 // Whether a step that reads `own` bytes of its layer reads them with
 // non-temporal loads. Steps of a layer read its pool in alternating
@@ -294,14 +302,17 @@ std::atomic<unsigned long long> g_streamed[kMaxDevices];
 // alone 41.2 / 45.2, with one more pool of that size in between 52.8 / 46.8;
 // 104 MB with 104, 208 and 312 MB in between 20.6 / 22.3, 23.4 / 22.9 and 25.8
 // / 23.2; 138 MB with 138 and 276 MB in between 28.1 / 30.9 and 34.7 / 31.2;
-// 335 MB alone 62.4 / 65.9, 402 MB alone 69.9 / 68.0). A layer's first step counts the pool's other
-// layers; a deterministic pool always does, so that its instance, and with it
-// the rounding, depends on nothing outside it.
-bool non_temporal(raas_pool* p, int layer, double own) {
-    const unsigned long long before = p->streamed_at[layer], now = g_streamed[p->device].fetch_add(
-        (unsigned long long)own, std::memory_order_relaxed);
-    const double others = before == 0 || p->cfg.deterministic ? (p->cfg.n_layers - 1.0) * own : (double)(now - before);
-    p->streamed_at[layer] = now + (unsigned long long)own;
+// 335 MB alone 62.4 / 65.9, 402 MB alone 69.9 / 68.0). A layer's first step
+// counts the pool's other layers; a deterministic pool always does, so that its
+// instance, and with it the rounding, depends on nothing outside it; so does a
+// captured step, whose replays take the load kind that the capture froze and
+// are not seen here (captured after other pools' steps and replayed alone, the
+// 268 MB pool would keep the 45.2 us of its kind).
+bool non_temporal(const raas_pool* p, int layer, double own, bool captured) {
+    const unsigned long long before = p->streamed_at[layer];
+    double others = (p->cfg.n_layers - 1.0) * own;
+    if (before != 0 && !p->cfg.deterministic && !captured)
+        others = (double)(g_streamed[p->device].load(std::memory_order_relaxed) - before);
     return others + own * 2.0 / 3.0 > 256e6;
 }
 
@@ -379,7 +390,9 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
     // to be still in the GPU's memory-side cache.
     L.rev = p->descending[layer];
     // keys and values of the blocks the step attends, and the prompt pages' representative keys
-    L.nt = non_temporal(p, layer, 2.0 * p->U * p->D * p->esz * ((double)work_blocks * kBlockTokens + p->npr));
+    const double own = 2.0 * p->U * p->D * p->esz * ((double)work_blocks * kBlockTokens + p->npr);
+    const bool captured = capturing(s);
+    L.nt = non_temporal(p, layer, own, captured);
     const bool prof = !fixed_scratch;
 
     if (select_kernel) {  // Quest on the prompt: which prompt pages this step attends to
@@ -403,6 +416,10 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
     if (e != hipSuccess) return hip_fail(e, "step launch");
     p->descending[layer] ^= 1;
     p->steps[layer] += 1;
+    if (!captured) {
+        const unsigned long long bytes = (unsigned long long)own;
+        p->streamed_at[layer] = bytes + g_streamed[p->device].fetch_add(bytes, std::memory_order_relaxed);
+    }
     p->last_stream = s;
     return RAAS_OK;
 }

@@ -201,3 +201,57 @@ def test_graph_replays(kw, splits, opt):
     say("case graph replays %s %s %s" % (kw, splits, opt))
     for p in pools:
         p.close()
+
+
+def _captured_kernels(step):
+    """Host functions of the kernels that a captured call launches."""
+    import ctypes
+
+    import torch
+
+    class Params(ctypes.Structure):  # hipKernelNodeParams
+        _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                    ("grid", ctypes.c_uint * 3), ("args", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(x.split()[-1] for x in f if "libamdhip64" in x))
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        step()
+    raw, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        p = Params()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        out.append((p.func, tuple(p.grid)))
+    return out
+
+
+def test_captured_load_kind_is_the_pool_s_own():
+    """What other pools streamed before a capture does not choose the captured
+    step's kernel: its replays take the kind that the pool alone would."""
+    import torch
+
+    say("case captured load kind")
+    w, big = _w(batch=8, budget=256), synth.get_workload("llama8b-b32-L2048")
+    pools = [new_pool(w), new_pool(big)]
+    steps = []
+    for x, pool in zip((w, big), pools):
+        kv = torch.zeros(x.batch, x.n_kv_heads, x.budget - 32, x.head_dim, dtype=torch.bfloat16, device="cuda")
+        pool.prefill(0, kv, kv)
+        q = torch.zeros(x.batch, x.n_q_heads, x.head_dim, dtype=torch.bfloat16, device="cuda")
+        new = torch.zeros(x.batch, x.n_kv_heads, x.head_dim, dtype=torch.bfloat16, device="cuda")
+        out = torch.empty_like(q)
+        steps.append(lambda pool=pool, q=q, new=new, out=out: pool.decode_step_static(0, q, new, new, out))
+    steps[0]()
+    alone = _captured_kernels(steps[0])
+    steps[0]()
+    for _ in range(3):  # 0.8 GB between two steps of the small pool
+        steps[1]()
+    torch.cuda.synchronize()
+    assert _captured_kernels(steps[0]) == alone and len(alone) == 1
+    for pool in pools:
+        pool.close()
