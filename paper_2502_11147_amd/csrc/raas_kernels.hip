@@ -852,20 +852,25 @@ __device__ __forceinline__ void retention_wave(const LayerView& L, const UnitRec
     const int k = (int)floor(r * (double)n);
     if (k > 0) {
         // two scores per LDS read (s_score is 16-byte aligned; slots below lo
-        // hold +inf), and the last of an odd S
+        // hold +inf), and the last of an odd S. The adds are one chain per
+        // counter, hence two; unrolled by 8 (one counter) 64 slots took as long
+        // as one score per read (8 units, 64 slots, us per step: one per read
+        // 13.23, two with one counter 13.30, so 13.14; 1 unit, 48 slots 12.18,
+        // 12.01, 11.94; 1 unit, 112 slots 17.56, 16.31, 15.70)
         const double2* sc2 = reinterpret_cast<const double2*>(s_score);
         const double last = (S & 1) ? s_score[S - 1] : INFINITY;
         for (int s0 = s_lo; s0 < S; s0 += 64) {
             const int p = s0 + lane;
             if (p < S && s_state[p] == kEvictable) {
                 const double sp = s_score[p];
-                int less = last < sp ? 1 : 0;
-#pragma unroll 8
+                int less = last < sp ? 1 : 0, less1 = 0;
+#pragma unroll 4
                 for (int o = s_lo >> 1; o < S >> 1; ++o) {
                     const double2 x = sc2[o];
-                    less += (x.x < sp ? 1 : 0) + (x.y < sp ? 1 : 0);
+                    less += x.x < sp ? 1 : 0;
+                    less1 += x.y < sp ? 1 : 0;
                 }
-                if (less >= n - k) s_ts[p] = ur.clock;
+                if (less + less1 >= n - k) s_ts[p] = ur.clock;
             }
         }
     }
