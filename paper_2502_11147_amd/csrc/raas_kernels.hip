@@ -663,8 +663,13 @@ __device__ __forceinline__ uint32_t mag_floor(uint32_t x) {
 // Written to lo/hi, with (-inf, inf) where a sum is not finite. Each
 // wavefront takes tiles w, w + NW, ..., TPW of them loaded at once. q_ops:
 // this lane's query operands (heads as columns). issue: the caller's loads,
-// issued behind the last round of tiles on every wavefront.
-template <int D, int NW, bool NT, class Issue>
+// issued behind the last round of tiles on every wavefront. The keys are read
+// with ordinary loads whatever the step's blocks are read with: a lane takes 16
+// bytes of a row at a time, and every step reads the same keys (us per step
+// among pools of 0.8 GB, non-temporal / ordinary: 64 units, 256 pages, 8 decode
+// blocks 28.1 / 26.4; 128 units, 512 pages, 32 blocks, three pools in turn 45.9 /
+// 42.6; 256 units, 256 pages, 8 blocks, the other way, 31.9 / 32.7).
+template <int D, int NW, class Issue>
 __device__ __forceinline__ void prompt_bounds(const LayerView& L, size_t base, int npages, const bf16x8 (&q_ops)[D / 32],
                                               float* lo, float* hi, Issue&& issue) {
     constexpr int KS = D / 32, TPW = D >= 128 ? 2 : 4;
@@ -700,13 +705,8 @@ __device__ __forceinline__ void prompt_bounds(const LayerView& L, size_t base, i
             for (int ks = 0; ks < KS; ++ks) {
                 const uint16_t* px = (const uint16_t*)L.kmax + off + 32 * ks;
                 const uint16_t* pn = (const uint16_t*)L.kmin + off + 32 * ks;
-                if constexpr (NT) {
-                    ax[h][ks] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(px));
-                    an[h][ks] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(pn));
-                } else {
-                    ax[h][ks] = ld4(px);
-                    an[h][ks] = ld4(pn);
-                }
+                ax[h][ks] = ld4(px);
+                an[h][ks] = ld4(pn);
             }
         }
     };
@@ -1715,7 +1715,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
         // block 0 and drops it (loads on every path keep the waits for the
         // tiles short of the block)
         auto first = [&]() { load_block(real(b) ? b : 0, kr_next, vr_next); };
-        if (L.dbase > L.topk) prompt_bounds<D, NW, NT>(L, base, L.dbase, qv, s_plo, s_phi, first);
+        if (L.dbase > L.topk) prompt_bounds<D, NW>(L, base, L.dbase, qv, s_plo, s_phi, first);
         else first();
     } else {
         if (real(b)) load_block(b, kr_next, vr_next);
@@ -2258,7 +2258,7 @@ __global__ __launch_bounds__(64) void k_prompt_intervals(LayerView L, StepIO io)
         qv[ks] = __builtin_bit_cast(bf16x8, x);
     }
     float* lo = L.pivl + (size_t)u * L.dbase + p0;
-    prompt_bounds<D, 1, false>(L, (size_t)u * L.S + p0, n, qv, lo, lo + (size_t)L.U * L.dbase, [] {});
+    prompt_bounds<D, 1>(L, (size_t)u * L.S + p0, n, qv, lo, lo + (size_t)L.U * L.dbase, [] {});
 }
 
 // The same selection for bf16 pools, on the MFMA: each kept prompt page's
@@ -2324,7 +2324,7 @@ __global__ __launch_bounds__(NW * 64) void k_prompt_select_mfma(LayerView L, Ste
                 s_phi[p] = ghi[p];
             }
         } else {
-            prompt_bounds<D, NW, false>(L, base, kp, qv, s_plo, s_phi, [] {});
+            prompt_bounds<D, NW>(L, base, kp, qv, s_plo, s_phi, [] {});
         }
     }
     __syncthreads();
