@@ -101,10 +101,14 @@ struct StepPlan {
 // unchosen prompt blocks); grouped: retention decided per group of units, by
 // the group's last workgroup;
 // list_ints: LDS ints of a block list or of the in-step prompt selection (0
-// without a prompt region)
+// without a prompt region); cold: little of the layer is still in the
+// memory-side cache (the step reads it with non-temporal loads)
 StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool bf16, int agg,
                    bool grouped, int list_ints, int split_override,
-                   int npr, int nkv);
+                   int npr, int nkv, bool cold);
+// Whether a step that reads `own` bytes of its layer, `others` bytes having
+// been streamed since the layer's last step, takes non-temporal loads.
+bool non_temporal_loads(double own, double others);
 // Quest on the prompt pages: the attended fills and the block list of a step.
 hipError_t launch_prompt_select(const LayerView& L, const StepIO& io, hipStream_t stream);
 // Lets the step kernels use more than the default dynamic LDS.

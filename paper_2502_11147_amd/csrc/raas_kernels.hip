@@ -2538,22 +2538,38 @@ RAAS_STEP(float, 64, 4, true)
 // workgroups, the last of which finishes the step. A split workgroup pays for
 // its start and for publishing (about 8 us, of which the last one's finish is
 // 4), so splits pay only where they put idle CUs to work, in one round:
-// 256 / U workgroups per unit at most, and none from 129 units on (192 units,
-// L 2048: 42.7 us fused, 59.1 in two; 192 units, L 8192: 118 against 137 to
-// 163 at any split). Below, a unit is split when it has more blocks than
-// kFusedBlocks (us per step, page 16, sixteen pools in turn so that none is
-// cached, fused against split: 8 units, 32 blocks 14.4 / 14.5, 64 blocks 19.7 /
-// 15.1; 32 units, 32 blocks 17.1 / 16.8, 48 blocks 23.6 / 18.9, 64 blocks 28.2
-// / 19.8; 64 units, 32 blocks 19.4 / 19.8, 48 blocks 25.2 / 22.9, 64 blocks
-// 30.3 / 24.7; 96 units, 64 blocks 33.6 / 31.0); from kHalfUnits on, where
-// two workgroups per unit fill the chip, when it has more than
-// kFusedBlocksHalf (128 units: 64 blocks 34.4 / 35.9, 128 blocks 60.6 / 59.5,
-// 256 blocks 95.4 / 91.1). More than kSplits splits, or fewer than 8 blocks in
-// one, no longer help (8 units: 64 blocks 15.1 in 8 and 15.3 in 16; 256 blocks
-// 26.1 in 4, 21.3 in 8, 19.2 in 16, 21.0 in 32). An fp32 block costs more
-// arithmetic, so fp32 units split at half as many (8 units, 32 blocks 18.9 /
-// 14.2; 64 units 22.0 / 18.8; 128 units, 32 blocks 25.5 / 27.0, 64 blocks 38.6
-// / 37.5).
+// 256 / U workgroups per unit at most, and none from 129 units on (fused / in
+// two, cold: 129 units, 64 blocks 30.6 / 49.8, 256 blocks 95.3 / 129.8; 160
+// units, 128 blocks 55.6 / 79.8; 192 units, L 8192: 118 against 137 to 163 at
+// any split). Below, a unit is split when it has more blocks than
+// fused_limit: kFusedBlocks where idle CUs stream what one would have to, more
+// where the publishing, which grows with G, or head_dim 64's shorter blocks
+// leave less to gain, and more again for many units that are still cached.
+// us per step, fused / split, page 16, one pool alone (cached) and 0.8 GB of
+// pools in turn (cold):
+//   G 4    8 units, 40 blocks  14.7 / 14.0 cached, 15.9 / 14.5 cold
+//         32 units, 48 blocks  16.2 / 15.5, 22.3 / 17.1
+//         48 units, 33 blocks  14.5 / 14.5, 18.6 / 17.1
+//         64 units, 40 blocks  15.3 / 15.8, 21.1 / 18.9
+//         64 units, 48 blocks  16.4 / 16.3 (three in turn, still cached, 17.4 / 18.9), 23.4 / 19.9
+//        112 units, 48 blocks  18.5 / 20.5, 25.1 / 24.6
+//   G 8    8 units, 40 blocks  16.3 / 16.7, 17.4 / 17.1
+//         64 units, 48 blocks  18.0 / 19.4, 24.8 / 22.3
+//   G 16   8 units, 48 blocks  20.2 / 22.5, 21.5 / 22.9
+//         32 units, 48 blocks  20.7 / 23.7, 26.7 / 25.3
+//   G 7, head_dim 64: 8 units, 48 blocks 12.7 / 13.3, 12.9 / 13.3; 64 units 13.0 / 14.4, 15.6 / 16.3
+// Two workgroups per unit still fit the chip's 256 CUs up to 128 units, but
+// from kHalfUnits on the first of them no longer gains enough when cold for what
+// it loses when cached, up to kFusedBlocksHalf blocks (G 4, fused / split: 112
+// units, 64 blocks 22.4 / 24.3 cached, 32.1 / 29.4 cold; 120 units 23.2 / 25.2,
+// 33.2 / 30.7; 124 units 24.0 / 26.3, 31.8 / 31.0; 128 units 24.2 / 26.4, 30.6
+// / 32.1; 120 units, 56 blocks 21.1 / 23.1, 28.2 / 27.9; 116 units, 49 blocks
+// 19.2 / 21.0, 25.6 / 25.3; 128 units, 256 blocks 95.4 / 91.1 cold). More than
+// kSplits splits, or fewer than 8 blocks in one, no longer help (8 units: 64
+// blocks 15.1 in 8 and 15.3 in 16; 256 blocks 26.1 in 4, 21.3 in 8, 19.2 in 16,
+// 21.0 in 32). An fp32 block costs more arithmetic, so fp32 units split at half
+// as many (8 units, 32 blocks 18.9 / 14.2; 64 units 22.0 / 18.8; 128 units, 32
+// blocks 25.5 / 27.0, 64 blocks 38.6 / 37.5).
 constexpr int kFusedBlocks = 32;
 constexpr int kHalfUnits = 113;
 constexpr int kFusedBlocksHalf = 64;
@@ -2581,8 +2597,23 @@ constexpr int kFusedPromptPages = 512;
 constexpr int kSmallWorkUnits = 1024;
 constexpr int kSmallWorkBlocks = 32;
 
+// Most blocks that one workgroup attends for a unit (the measurements are at
+// kFusedBlocks). long_prompt: a prompt region of more than kFusedPromptPages,
+// whose slots the last workgroup of a split unit would all read again (64
+// units, 1536 pages, 40 blocks: 57.4 us before, 58.7 split, 52.5 fused).
+int fused_limit(int U, int G, int D, int S, bool bf16, bool long_prompt, bool cold) {
+    if (!bf16) return (U < kHalfUnits ? kFusedBlocks : kFusedBlocksHalf) / 2;
+    if (U >= kHalfUnits) return kFusedBlocksHalf;
+    const int most = S <= kFewSlots ? 64 : 48;
+    if (long_prompt) return most;
+    if (D == 64) return G <= 8 && U <= (cold ? 64 : 16) ? 48 : most;
+    if (cold) return G <= 8 ? (U <= 48 ? kFusedBlocks : 39) : U <= 64 ? 47 : most;
+    if (G <= 4) return U <= 32 ? kFusedBlocks : U <= 48 ? 48 : most;
+    return U <= 16 ? (G <= 8 ? 40 : std::min(56, most)) : most;
+}
+
 StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool bf16, int agg,
-                   bool grouped, int list_ints, int split_override, int npr, int nkv) {
+                   bool grouped, int list_ints, int split_override, int npr, int nkv, bool cold) {
     StepPlan pl{};
     const int nblk = Lcap / kBlockTokens;
     // blocks of 16 KB (head_dim 128): 32 tokens in bf16, 16 in fp32
@@ -2609,7 +2640,8 @@ StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool b
         pl.waves == 4 && 4 * step_lds(G, D, S, 2, true, agg, list_ints) <= kMaxLds)
         pl.waves = 2;
     const bool fits = !grouped && step_lds(G, D, S, pl.waves, true, agg, list_ints) <= kMaxLds;
-    const int fused_blocks = (U < kHalfUnits ? kFusedBlocks : kFusedBlocksHalf) / (bf16 ? 1 : 2);
+    const bool many_prompt_slots = list_ints > 0 && npr > kFusedPromptPages;
+    const int fused_blocks = fused_limit(U, G, D, S, bf16, many_prompt_slots, cold);
     if (split_override > 0) {
         want = split_override;
     } else if (fits && bf16 && list_ints > 0 && !agg && U < 256 && npr <= kFusedPromptPages &&
@@ -2618,8 +2650,9 @@ StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool b
         // pages itself and attends the chosen blocks and the decode ones,
         // which saves the selection kernel's launch as well
         want = 1;
-    } else if (fits && work <= fused_blocks && (list_ints == 0 || agg || !bf16 || npr <= kFusedPromptPages)) {
-        want = 1;
+    } else if (work <= fused_blocks && (fits || (many_prompt_slots && bf16 && !grouped)) &&
+               (!many_prompt_slots || agg || !bf16)) {
+        want = 1;  // (with many prompt slots also where the fused LDS does not fit)
     } else {
         want = std::min(std::min(std::max(256 / U, 1), kSplits), (work + 7) / 8);
     }

@@ -18,6 +18,17 @@
 
 using namespace raas;
 
+// Steps of a layer read its pool in alternating directions, so what the
+// memory-side cache (256 MB) still holds of it is the cache less what other
+// layers and pools have streamed since; when that is less than two thirds of
+// the layer, non-temporal loads are the faster ones, which leave the cache alone
+// (us per step, ordinary / non-temporal: 268 MB alone 41.2 / 45.2, with one more
+// pool of that size in between 52.8 / 46.8; 104 MB with 104, 208 and 312 MB in
+// between 20.6 / 22.3, 23.4 / 22.9 and 25.8 / 23.2; 138 MB with 138 and 276 MB in
+// between 28.1 / 30.9 and 34.7 / 31.2; 335 MB alone 62.4 / 65.9, 402 MB alone
+// 69.9 / 68.0).
+bool raas::non_temporal_loads(double own, double others) { return others + own * 2.0 / 3.0 > 256e6; }
+
 namespace {
 
 thread_local std::string g_last_error;
@@ -293,27 +304,18 @@ bool capturing(hipStream_t s) {
     return st != hipStreamCaptureStatusNone;
 }
 
-// Whether a step that reads `own` bytes of its layer reads them with
-// non-temporal loads. Steps of a layer read its pool in alternating
-// directions, so what the memory-side cache (256 MB) still holds of it is the
-// cache less what other layers and pools have streamed since; when that is
-// less than two thirds of the layer, non-temporal loads are the faster ones,
-// which leave the cache alone (us per step, ordinary / non-temporal: 268 MB
-// alone 41.2 / 45.2, with one more pool of that size in between 52.8 / 46.8;
-// 104 MB with 104, 208 and 312 MB in between 20.6 / 22.3, 23.4 / 22.9 and 25.8
-// / 23.2; 138 MB with 138 and 276 MB in between 28.1 / 30.9 and 34.7 / 31.2;
-// 335 MB alone 62.4 / 65.9, 402 MB alone 69.9 / 68.0). A layer's first step
+// The load kind of a step. A layer's first step
 // counts the pool's other layers; a deterministic pool always does, so that its
 // instance, and with it the rounding, depends on nothing outside it; so does a
 // captured step, whose replays take the load kind that the capture froze and
-// are not seen here (captured after other pools' steps and replayed alone, the
-// 268 MB pool would keep the 45.2 us of its kind).
+// are not seen here (captured after other pools' steps and replayed alone, a
+// 268 MB pool would keep non-temporal loads, 45.2 us a step for 41.2).
 bool non_temporal(const raas_pool* p, int layer, double own, bool captured) {
     const unsigned long long before = p->streamed_at[layer];
     double others = (p->cfg.n_layers - 1.0) * own;
     if (before != 0 && !p->cfg.deterministic && !captured)
         others = (double)(g_streamed[p->device].load(std::memory_order_relaxed) - before);
-    return others + own * 2.0 / 3.0 > 256e6;
+    return raas::non_temporal_loads(own, others);
 }
 
 // One decode step of one layer (raas_decode_step_masked); with
@@ -338,10 +340,14 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
         const int per_page = std::max(1, p->ps / kBlockTokens);
         work_blocks = L.nblk - nbp + std::min(nbp, p->cfg.prompt_topk * per_page);
     }
+    // keys and values of the blocks the step attends, and the prompt pages' representative keys
+    const double own = 2.0 * p->U * p->D * p->esz * ((double)work_blocks * kBlockTokens + p->npr);
+    const bool captured = capturing(s);
+    L.nt = non_temporal(p, layer, own, captured);
     const StepPlan pl = plan_step(p->U, p->G, p->D, p->S, L.nblk * kBlockTokens, work_blocks,
                                   p->cfg.dtype == RAAS_BF16, p->cfg.score_aggregation,
                                   p->cfg.decision_scope == RAAS_SCOPE_SEQUENCE, list_ints(p), p->split_override, p->npr,
-                                  p->cfg.n_kv_heads);
+                                  p->cfg.n_kv_heads, L.nt != 0);
     L.nsplit = pl.nsplit;
     L.bps = pl.bps;
     // the first score pass issued with the first blocks: the score barrier and
@@ -389,10 +395,6 @@ raas_status decode_step(raas_pool* p, int32_t layer, const StepIO& io, hipStream
     // step starts with the blocks the previous one read last, the likeliest
     // to be still in the GPU's memory-side cache.
     L.rev = p->descending[layer];
-    // keys and values of the blocks the step attends, and the prompt pages' representative keys
-    const double own = 2.0 * p->U * p->D * p->esz * ((double)work_blocks * kBlockTokens + p->npr);
-    const bool captured = capturing(s);
-    L.nt = non_temporal(p, layer, own, captured);
     const bool prof = !fixed_scratch;
 
     if (select_kernel) {  // Quest on the prompt: which prompt pages this step attends to
