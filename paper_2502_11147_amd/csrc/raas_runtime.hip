@@ -21,13 +21,18 @@ using namespace raas;
 // Steps of a layer read its pool in alternating directions, so what the
 // memory-side cache (256 MB) still holds of it is the cache less what other
 // layers and pools have streamed since; when that is less than two thirds of
-// the layer, non-temporal loads are the faster ones, which leave the cache alone
+// the layer (four sevenths where the units fill the CUs evenly), non-temporal
+// loads are the faster ones, which leave the cache alone
 // (us per step, ordinary / non-temporal: 268 MB alone 41.2 / 45.2, with one more
 // pool of that size in between 52.8 / 46.8; 104 MB with 104, 208 and 312 MB in
 // between 20.6 / 22.3, 23.4 / 22.9 and 25.8 / 23.2; 138 MB with 138 and 276 MB in
-// between 28.1 / 30.9 and 34.7 / 31.2; 335 MB alone 62.4 / 65.9, 402 MB alone
-// 69.9 / 68.0).
-bool raas::non_temporal_loads(double own, double others) { return others + own * 2.0 / 3.0 > 256e6; }
+// between 28.1 / 30.9 and 34.7 / 31.2; alone, 256 units of 403, 436 and 470 MB
+// 62.6 / 65.3, 68.7 / 70.0 and 74.3 / 74.6, 512 units of 403 and 470 MB 66.3 /
+// 67.2 and 77.5 / 77.8; 192, 384 and 640 units of 403 to 419 MB 63.0 / 61.5,
+// 68.6 / 66.6 and 80.2 / 77.3).
+bool raas::non_temporal_loads(double own, double others, int units) {
+    return others + own * (units % 256 == 0 ? 4.0 / 7.0 : 2.0 / 3.0) > 256e6;
+}
 
 namespace {
 
@@ -315,7 +320,7 @@ bool non_temporal(const raas_pool* p, int layer, double own, bool captured) {
     double others = (p->cfg.n_layers - 1.0) * own;
     if (before != 0 && !p->cfg.deterministic && !captured)
         others = (double)(g_streamed[p->device].load(std::memory_order_relaxed) - before);
-    return raas::non_temporal_loads(own, others);
+    return raas::non_temporal_loads(own, others, p->U);
 }
 
 // One decode step of one layer (raas_decode_step_masked); with

@@ -76,11 +76,12 @@ def test_small_units_leave_the_fixed_array_alone(ask):
                                  _plan(8, 25, bf16=0, page=8)])] == [0, 0, 1, 0]
 
 
-# bytes of the layer, bytes streamed since its last step, non-temporal loads
-LOADS = [(268e6, 0, 0), (268e6, 268e6, 1), (104e6, 104e6, 0), (104e6, 208e6, 1), (138e6, 138e6, 0), (138e6, 276e6, 1),
-         (335e6, 0, 0), (537e6, 0, 1)]
+# units, bytes of the layer, bytes streamed since its last step, non-temporal loads
+LOADS = [(256, 268e6, 0, 0), (256, 268e6, 268e6, 1), (104, 104e6, 104e6, 0), (104, 104e6, 208e6, 1),
+         (128, 138e6, 138e6, 0), (128, 138e6, 276e6, 1), (256, 335e6, 0, 0), (256, 436e6, 0, 0), (256, 470e6, 0, 1),
+         (512, 403e6, 0, 0), (384, 370e6, 0, 0), (384, 403e6, 0, 1), (1024, 537e6, 0, 1)]
 
 
-@pytest.mark.parametrize("own,others,nt", LOADS)
-def test_load_kind(ask, own, others, nt):
-    assert ask(["loads %r %r" % (own, others)]) == [(nt,)]
+@pytest.mark.parametrize("units,own,others,nt", LOADS)
+def test_load_kind(ask, units, own, others, nt):
+    assert ask(["loads %r %r %d" % (own, others, units)]) == [(nt,)]
