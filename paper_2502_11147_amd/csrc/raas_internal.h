@@ -111,8 +111,11 @@ StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool b
 bool non_temporal_loads(double own, double others, int units);
 // Quest on the prompt pages: the attended fills and the block list of a step.
 hipError_t launch_prompt_select(const LayerView& L, const StepIO& io, hipStream_t stream);
-// Lets the step kernels use more than the default dynamic LDS.
-hipError_t allow_large_lds();
+// Lets the step kernels of a pool's type, head_dim and group size use more than
+// the default dynamic LDS (a call per instance, and the first one loads its
+// code: all types' instances made a process's first pool 16 ms, one type's 4.5,
+// and a later one 0.105 ms against 0.083).
+hipError_t allow_large_lds(bool bf16, int D, int G);
 
 // Launchers (asynchronous on `stream`; return the launch status).
 // max_tok: the most tokens any selected unit keeps (min(P, kept pages * ps)).

@@ -2424,7 +2424,8 @@ size_t step_lds(int G, int D, int S, int NW, bool fused, int agg, int list_ints)
 
 // Every instance of the step kernel for one type, head_dim and workgroup size.
 // f(pointer) is called for the one that the layer and plan ask for, or (all)
-// for each.
+// for each. Workgroups of 2 wavefronts always cover their unit (plan_step: from
+// kSmallWorkUnits on), so they have no split instances.
 template <typename T, int D, int NW, bool G4, class F>
 void each_step(bool all, bool agg, int lm, bool nt, bool split, F&& f) {
     auto one = [&](auto A, auto M, auto N, auto P) {
@@ -2434,8 +2435,10 @@ void each_step(bool all, bool agg, int lm, bool nt, bool split, F&& f) {
         }
     };
     auto nts = [&](auto A, auto M, auto P) {
-        one(A, M, std::false_type{}, P);
-        one(A, M, std::true_type{}, P);
+        if constexpr (NW > 2 || !P.value) {
+            one(A, M, std::false_type{}, P);
+            one(A, M, std::true_type{}, P);
+        }
     };
     const std::integral_constant<int, 0> m0{};
     const std::integral_constant<int, 1> m1{};
@@ -2459,10 +2462,12 @@ template <typename T, int D, int NW, bool G4>
 hipError_t launch_step_inst(const LayerView& L, const StepIO& io, const StepPlan& pl, float sl2, double r,
                             hipStream_t s) {
     const int lm = pl.select_in_step ? 2 : L.topk >= 0 ? 1 : 0;
+    bool found = false;
     each_step<T, D, NW, G4>(false, L.agg != 0, lm, L.nt != 0, !pl.fused, [&](auto* kernel) {
+        found = true;
         hipLaunchKernelGGL(kernel, dim3((unsigned)(L.U * pl.nsplit)), dim3(NW * 64), pl.lds, s, L, io, sl2, r);
     });
-    return hipGetLastError();
+    return found ? hipGetLastError() : hipErrorInvalidDeviceFunction;
 }
 
 template <typename T, int D, int NW, bool G4>
@@ -2678,19 +2683,28 @@ StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool b
     return pl;
 }
 
-hipError_t allow_large_lds() {
+hipError_t allow_large_lds(bool bf16, int D, int G) {
     const int bytes = (int)kMaxLds;
-    hipError_t e = hipSuccess;
-    for (hipError_t r :
-         {allow_lds_all<uint16_t, 128, 8, false>(bytes), allow_lds_all<uint16_t, 128, 4, false>(bytes),
-          allow_lds_all<uint16_t, 128, 2, false>(bytes), allow_lds_all<uint16_t, 64, 8, false>(bytes),
-          allow_lds_all<uint16_t, 64, 4, false>(bytes), allow_lds_all<uint16_t, 64, 2, false>(bytes),
-          allow_lds_all<float, 128, 8, false>(bytes), allow_lds_all<float, 128, 8, true>(bytes),
-          allow_lds_all<float, 128, 4, false>(bytes), allow_lds_all<float, 128, 4, true>(bytes),
-          allow_lds_all<float, 64, 8, false>(bytes), allow_lds_all<float, 64, 8, true>(bytes),
-          allow_lds_all<float, 64, 4, false>(bytes), allow_lds_all<float, 64, 4, true>(bytes)})
-        if (r != hipSuccess) e = r;
-    return e;
+    if (bf16) {
+        hipError_t e = hipSuccess;
+        for (hipError_t r : {D == 128 ? allow_lds_all<uint16_t, 128, 8, false>(bytes) : allow_lds_all<uint16_t, 64, 8, false>(bytes),
+                             D == 128 ? allow_lds_all<uint16_t, 128, 4, false>(bytes) : allow_lds_all<uint16_t, 64, 4, false>(bytes),
+                             D == 128 ? allow_lds_all<uint16_t, 128, 2, false>(bytes) : allow_lds_all<uint16_t, 64, 2, false>(bytes)})
+            if (r != hipSuccess) e = r;
+        return e;
+    }
+    auto f32 = [&](auto d, auto g4) {
+        constexpr int DD = decltype(d)::value;
+        constexpr bool G4 = decltype(g4)::value;
+        const hipError_t r = allow_lds_all<float, DD, 8, G4>(bytes), q = allow_lds_all<float, DD, 4, G4>(bytes);
+        return r != hipSuccess ? r : q;
+    };
+    const std::integral_constant<int, 128> d128{};
+    const std::integral_constant<int, 64> d64{};
+    const std::true_type yes{};
+    const std::false_type no{};
+    if (G <= 4) return D == 128 ? f32(d128, yes) : f32(d64, yes);
+    return D == 128 ? f32(d128, no) : f32(d64, no);
 }
 
 template <typename T, int GQ>

@@ -491,7 +491,7 @@ raas_status raas_create_pool(const raas_config* cfg, void* stream, raas_pool** o
         {(void**)&p->pivl, p->npr > 0 ? 2 * (size_t)p->U * p->npr * sizeof(float) : 4},
     };
     hipStream_t s = (hipStream_t)stream;
-    hipError_t ea = allow_large_lds();
+    hipError_t ea = allow_large_lds(cfg->dtype == RAAS_BF16, p->D, p->G);
     if (ea != hipSuccess) {
         raas_destroy(p);
         return hip_fail(ea, "hipFuncSetAttribute");

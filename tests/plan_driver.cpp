@@ -15,7 +15,7 @@ int main() {
                    &splits, &npr, &cold) == 12) {
             const raas::StepPlan p = raas::plan_step(U, G, D, S, blocks * raas::kBlockTokens, work, bf16 != 0, agg, false,
                                                      list, splits, npr, 1, cold != 0);
-            printf("%d %d %d\n", p.waves, p.nsplit, p.pool_scratch ? 1 : 0);
+            printf("%d %d %d %d\n", p.waves, p.nsplit, p.pool_scratch ? 1 : 0, p.fused ? 1 : 0);
         } else if (sscanf(line, "loads %lf %lf %d", &own, &others, &U) == 3) {
             printf("%d\n", raas::non_temporal_loads(own, others, U) ? 1 : 0);
         } else {

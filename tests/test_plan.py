@@ -63,7 +63,7 @@ SPLITS = [
 
 @pytest.mark.parametrize("kw,split", SPLITS, ids=[",".join("%s=%s" % kv for kv in k.items()) for k, _ in SPLITS])
 def test_split_rule(ask, kw, split):
-    (waves, nsplit, _), = ask([_plan(**kw)])
+    (waves, nsplit, _, _), = ask([_plan(**kw)])
     assert (nsplit > 1) == split and waves == (8 if kw["U"] <= 256 else 4)
 
 
@@ -74,6 +74,16 @@ def test_small_units_leave_the_fixed_array_alone(ask):
     assert all(p[2] == 1 for p in ask(lines))
     assert [p[2] for p in ask([_plan(8, 49), _plan(8, 40, splits=3), _plan(8, 24, bf16=0, page=8),
                                  _plan(8, 25, bf16=0, page=8)])] == [0, 0, 1, 0]
+
+
+def test_two_wavefronts_cover_their_unit(ask):
+    """There are no split instances for workgroups of 2 wavefronts."""
+    lines = [_plan(u, b, G=g, D=d, agg=a, npr=n, cold=c, page=p) for u in (1023, 1024, 5000) for b in (1, 8, 32, 33)
+             for g in (1, 4, 7, 16) for d in (64, 128) for a in (0, 1) for n in (0, 64, 512, 1024) for c in (0, 1)
+             for p in (16, 32)]
+    plans = ask(lines)
+    assert any(p[0] == 2 for p in plans)
+    assert all(p[1] == 1 and p[3] == 1 for p in plans if p[0] == 2)
 
 
 # units, bytes of the layer, bytes streamed since its last step, non-temporal loads
