@@ -76,6 +76,12 @@ __device__ __forceinline__ size_t v_off(int t, int c) {
 }
 
 __device__ __forceinline__ u32x4 ld4(const void* p) { return *reinterpret_cast<const u32x4*>(p); }
+// The same from a caller's tensor, which is aligned to its element type only
+// (the hardware takes any address for a 16-byte global load).
+typedef uint32_t u32x4_at2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x4_at4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ u32x4 ld4_in(const uint16_t* p) { return *reinterpret_cast<const u32x4_at2*>(p); }
+__device__ __forceinline__ u32x4 ld4_in(const float* p) { return *reinterpret_cast<const u32x4_at4*>(p); }
 __device__ __forceinline__ void st4(void* p, u32x4 x) { *reinterpret_cast<u32x4*>(p) = x; }
 
 __device__ __forceinline__ uint16_t u16_at(const u32x4& x, int e) {
@@ -195,9 +201,9 @@ __global__ __launch_bounds__(kPrefillWaves * 64) void k_prefill(LayerView L, con
         const int t0 = t_tile + 8 * oct, n = min(max(keep - t0, 0), 8);  // this lane's tokens
         u32x4 kr[8], vr[8];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) kr[r] = r < n ? ld4(ku + (size_t)(t0 + r) * D) : u32x4{0u, 0u, 0u, 0u};
+        for (int r = 0; r < 8; ++r) kr[r] = r < n ? ld4_in(ku + (size_t)(t0 + r) * D) : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int r = 0; r < 8; ++r) vr[r] = r < n ? ld4(vu + (size_t)(t0 + r) * D) : u32x4{0u, 0u, 0u, 0u};
+        for (int r = 0; r < 8; ++r) vr[r] = r < n ? ld4_in(vu + (size_t)(t0 + r) * D) : u32x4{0u, 0u, 0u, 0u};
         if constexpr (REP) {  // per-channel min and max, the first of equals
 #pragma unroll
             for (int r = 0; r < 8; ++r)
@@ -1645,7 +1651,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
     // use into the branch, with a wait for it ahead of the block loads
     const T q_first = qg[tid < G * D ? tid : 0];
     const int t_new = tid < D / VE ? tid : 0;
-    const u32x4 kn_first = ld4(kn_g + VE * t_new), vn_first = ld4(vn_g + VE * t_new);
+    const u32x4 kn_first = ld4_in(kn_g + VE * t_new), vn_first = ld4_in(vn_g + VE * t_new);
     const int s_first = tid < S ? tid : 0;
     const int st_first = L.state[base + s_first], ts_first = L.ts[base + s_first], lid_first = L.lid[base + s_first];
     const int pf_first = LM == 2 ? fu[tid < L.dbase ? tid : 0] : 0;  // LM 2: a prompt page's fill
@@ -1662,7 +1668,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
     if constexpr (!F32) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            const u32x4 x = (col < G) ? ld4(qg + (size_t)col * D + 32 * ks + 8 * grp) : u32x4{0u, 0u, 0u, 0u};
+            const u32x4 x = (col < G) ? ld4_in(qg + (size_t)col * D + 32 * ks + 8 * grp) : u32x4{0u, 0u, 0u, 0u};
             qv[ks] = __builtin_bit_cast(bf16x8, x);
         }
     }
@@ -2254,7 +2260,7 @@ __global__ __launch_bounds__(64) void k_prompt_intervals(LayerView L, StepIO io)
     bf16x8 qv[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-        const u32x4 x = (col < L.G) ? ld4(qg + (size_t)col * D + 32 * ks + 8 * grp) : u32x4{0u, 0u, 0u, 0u};
+        const u32x4 x = (col < L.G) ? ld4_in(qg + (size_t)col * D + 32 * ks + 8 * grp) : u32x4{0u, 0u, 0u, 0u};
         qv[ks] = __builtin_bit_cast(bf16x8, x);
     }
     float* lo = L.pivl + (size_t)u * L.dbase + p0;
@@ -2294,7 +2300,7 @@ __global__ __launch_bounds__(NW * 64) void k_prompt_select_mfma(LayerView L, Ste
     bf16x8 qv[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-        const u32x4 x = (col < G) ? ld4(qg + (size_t)col * D + 32 * ks + 8 * grp) : u32x4{0u, 0u, 0u, 0u};
+        const u32x4 x = (col < G) ? ld4_in(qg + (size_t)col * D + 32 * ks + 8 * grp) : u32x4{0u, 0u, 0u, 0u};
         qv[ks] = __builtin_bit_cast(bf16x8, x);
     }
     for (int p = tid; p < npr; p += NT) s_sel[p] = p < kp ? 1 : 0;

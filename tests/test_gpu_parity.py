@@ -1104,3 +1104,36 @@ def test_prompt_selection_full_size(name, topk, steps, units):
                      prompt_tokens=w.prefill_len, prompt_topk=topk)
     _report(rep, name + " prompt-selection")
     assert rep.evictions > 0
+
+
+@pytest.mark.parametrize("dtype,opt", [("bf16", {}), ("bf16", dict(prompt_tokens=64, prompt_topk=2)), ("f32", {})],
+                         ids=["bf16", "bf16-prompt", "f32"])
+def test_inputs_aligned_to_their_elements_only(dtype, opt):
+    """Inputs one element past a 16-byte boundary give the aligned ones' bits."""
+    import torch
+
+    _say("case element-aligned inputs %s %s" % (dtype, opt))
+    w = small(dtype=dtype, prefill_len=60)
+    B, Hq, Hkv, d = w.batch, w.n_q_heads, w.n_kv_heads, w.head_dim
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def pair(*shape):
+        x = torch.randn(*shape, generator=g, device="cuda").to(dt)
+        buf = torch.empty(x.numel() + 8, dtype=dt, device="cuda")
+        y = buf[1:1 + x.numel()].view(*shape)
+        y.copy_(x)
+        assert x.data_ptr() % 16 == 0 and y.data_ptr() % 16 == x.element_size()
+        return x, y
+
+    pools = [new_pool(w, deterministic=True, **opt) for _ in range(2)]
+    k0, v0 = pair(B, Hkv, 60, d), pair(B, Hkv, 60, d)
+    for i, p in enumerate(pools):
+        p.prefill(0, k0[i], v0[i])
+    for t in range(24):
+        q, k, v, out = pair(B, Hq, d), pair(B, Hkv, d), pair(B, Hkv, d), pair(B, Hq, d)
+        for i, p in enumerate(pools):
+            p.decode_step(0, q[i], k[i], v[i], out[i])
+        assert torch.equal(*out), t
+    for p in pools:
+        p.close()
