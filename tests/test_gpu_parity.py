@@ -92,10 +92,10 @@ EDGE = [
     # r not exact in binary: floor(r * n) at n a multiple of 10 evictable pages
     # (3 pinned + 10 or 20 decode pages) is 7 and 18, one more than a float r gives
     dict(r=0.7, budget=16 * 13), dict(r=0.9, budget=16 * 23), dict(r=0.7, budget=16 * 13, dtype="f32"),
-    dict(r=0.9, page_size=8, budget=8 * 308, prefill_len=2300),   # 288 pinned + 20, the epilogue's radix select
+    dict(r=0.9, page_size=8, budget=8 * 308, prefill_len=2300),   # 288 pinned + 20
     dict(dtype="f32", head_dim=128),
     dict(dtype="f32", n_q_heads=14, n_kv_heads=2, head_dim=64, page_size=8, budget=96),
-    dict(page_size=8, budget=2400, prefill_len=2300),             # 300 slots: the epilogue's radix select
+    dict(page_size=8, budget=2400, prefill_len=2300),             # 300 slots, 12 past the pinned ones
     dict(page_size=8, budget=2400, prefill_len=2300, r=0.25),
     dict(page_size=8, budget=16384, prefill_len=16000, decode_steps=80),  # 2048 slots, the most a pool has
     dict(n_q_heads=32, n_kv_heads=2, head_dim=64, page_size=128, budget=1024, prefill_len=300),  # G 16, d 64, page 128
@@ -121,7 +121,7 @@ F32_SHAPES = [
     dict(budget=512, prefill_len=100, decode_steps=520, splits=1),   # eight chunks in one wavefront
     dict(budget=512, prefill_len=100, decode_steps=520, splits=3),   # uneven splits, ragged last chunk
     dict(budget=80, page_size=8, prefill_len=3, splits=2),       # ragged pages and chunks
-    # head_dim 64: one workgroup per unit, a wavefront per split, the epilogue in the same kernel
+    # head_dim 64: one workgroup per unit, as the other shapes
     dict(head_dim=64, budget=256, prefill_len=40, splits=1),     # one wavefront over four chunks
     dict(head_dim=64, budget=256, prefill_len=40, splits=3),     # uneven splits
     dict(head_dim=64, budget=512, prefill_len=100, decode_steps=520, splits=8),  # eight wavefronts
@@ -481,14 +481,14 @@ def test_stress_dense_equivalence():
 VARIANTS = [(0, True), (1, False), (1, True)]
 VARIANT_CASES = [
     dict(),                                                         # fused step kernel
-    dict(budget=512, prefill_len=100, decode_steps=520, splits=3),  # split path and epilogue kernel
+    dict(budget=512, prefill_len=100, decode_steps=520, splits=3),  # split path
     dict(dtype="f32"),
     dict(n_q_heads=28, n_kv_heads=4),                               # G = 7
     dict(n_q_heads=2, n_kv_heads=2),                                # G = 1
     dict(prefill_len=1000),                                         # S-1 pinned pages, one decode slot
     dict(prefill_len=0),                                            # nothing pinned
     dict(head_dim=64, page_size=8, budget=64, prefill_len=21),
-    dict(page_size=8, budget=2400, prefill_len=2300),               # 300 slots, radix select
+    dict(page_size=8, budget=2400, prefill_len=2300),               # 300 slots (ranked with the pinned ones: radix select)
     dict(page_size=8, budget=16384, prefill_len=16000, decode_steps=60),  # 2048 slots, 2047 of them pinned
 ]
 
@@ -511,7 +511,7 @@ def test_score_variants(agg, rank, case):
 def test_score_variants_full_size(name, steps, units, splits):
     """Both variants together at full size, in the benchmark's launch
     configuration (one fused workgroup per unit for both), and llama8b-b1
-    split over 4 workgroups per unit (the epilogue kernel)."""
+    split over 4 workgroups per unit."""
     w = synth.get_workload(name)
     _say("case variant agg 1 rank_pinned 1 %s steps %d splits %s" % (name, steps, splits))
     rep = run_parity(w, seed=1, steps=steps, units=_sample_units(w, units), out_every=32, chunk=128,
@@ -548,6 +548,77 @@ def test_split_unit_finish(case):
     _say("case split finish %s %s steps %d" % (case, run_kw, w.decode_steps))
     rep = run_parity(w, seed=21, steps=w.decode_steps, out_every=4, **run_kw)
     _report(rep, "split-finish")
+    assert rep.evictions > 0
+
+
+# The finish counts the slots past the pinned ones: with no prompt, every slot,
+# on both sides of its lines at 64, 128 and 256 and well into the radix select.
+@pytest.mark.parametrize("slots", [64, 65, 128, 129, 256, 257, 300])
+def test_split_unit_finish_every_slot(slots):
+    w = small(page_size=8, prefill_len=0, budget=8 * slots, decode_steps=8 * slots + 24, batch=1)
+    _say("case split finish, %d slots past the pinned" % slots)
+    rep = run_parity(w, seed=31, steps=w.decode_steps, splits=3, out_every=16)
+    _report(rep, "split-finish-every-slot")
+    assert rep.evictions > 0
+
+
+class _Busy:
+    """A pool whose steps t with t % 10 >= 5 come after a step of a 0.3 GB
+    pool: those take non-temporal loads, the others ordinary ones."""
+
+    def __init__(self, pool, other):
+        self._pool, self._other, self._t = pool, other, 0
+
+    def __getattr__(self, name):
+        return getattr(self._pool, name)
+
+    def decode_step(self, *args):
+        if self._t % 10 >= 5:
+            self._other()
+        self._t += 1
+        self._pool.decode_step(*args)
+
+
+@pytest.fixture(scope="module")
+def other_pool_step():
+    import torch
+
+    w = small(batch=32, n_q_heads=32, n_kv_heads=8, budget=2560, prefill_len=2528)
+    pool = new_pool(w)
+    z = lambda *shape: torch.zeros(*shape, dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    kv = z(w.batch, w.n_kv_heads, w.prefill_len, w.head_dim)
+    pool.prefill(0, kv, kv)
+    q, new = z(w.batch, w.n_q_heads, w.head_dim), z(w.batch, w.n_kv_heads, w.head_dim)
+    out = torch.empty_like(q)
+    args = pool.prepare_step(0, q, new, new, out)
+    yield lambda: pool.decode_prepared(args)
+    pool.close()
+
+
+_FORMS = [dict(), dict(splits=3), dict(aggregation=1), dict(aggregation=1, splits=3)]
+_LIST = dict(prompt_tokens=192, prompt_topk=4, prefill_len=190)
+BUSY_CASES = (
+    [dict(f, dtype="f32", head_dim=d, n_q_heads=2 * g) for d in (64, 128) for g in (4, 5) for f in _FORMS]
+    + [dict(f, **_LIST, dtype="f32", head_dim=d, n_q_heads=2 * g) for d in (64, 128) for g in (4, 5) for f in _FORMS]
+    + [dict(f, head_dim=d, n_q_heads=14) for d in (64, 128) for f in (_FORMS[1], _FORMS[3])]
+    + [dict(dtype="f32", head_dim=d, n_q_heads=2 * g, batch=130, page_size=8, budget=64) for d in (64, 128) for g in (4, 5)]
+    + [dict(n_q_heads=16, batch=6, budget=1280, prefill_len=1210)]  # 12 units of 40 blocks, G 8: split when cold
+)
+
+
+@pytest.mark.parametrize("case", BUSY_CASES, ids=[",".join("%s=%s" % kv for kv in c.items()) for c in BUSY_CASES])
+def test_load_kind_changes_mid_run(case, other_pool_step):
+    """Steps whose load kind, and with it the kernel instance and at the last
+    case the plan, changes every five steps."""
+    case = dict(case)
+    splits = case.pop("splits", None)
+    opts = {k: case.pop(k) for k in ("aggregation", "prompt_tokens", "prompt_topk") if k in case}
+    w = small(decode_steps=160, **case)
+    _say("case load kind mid-run %s %s splits %s" % (case, opts, splits))
+    pool = new_pool(w, splits, **opts)
+    rep = run_parity(w, seed=33, steps=w.decode_steps, out_every=3, pool=_Busy(pool, other_pool_step), **opts)
+    pool.close()
+    _report(rep, "load-kind")
     assert rep.evictions > 0
 
 
