@@ -32,7 +32,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
-KERNEL_STEP, KERNEL_EPILOGUE, KERNEL_SELECT = 0, 1, 2
+KERNEL_STEP, KERNEL_SELECT = 0, 2
 
 
 def parse():
@@ -370,9 +370,10 @@ def cold_row(w, args, kernel_bytes, steps=500, layers=4):
 
     fill = max(0, w.budget - w.prefill_len) + w.page_size
     run(0, fill + 50)
-    pool.profile(1 << KERNEL_EPILOGUE)
+    pool.profile((1 << KERNEL_STEP) | (1 << KERNEL_SELECT))
     run(fill + 50, 1)
-    assert pool.profile_read(KERNEL_EPILOGUE)[1] == 0, "expected one fused kernel per step"
+    launches = pool.profile_read(KERNEL_STEP)[1], pool.profile_read(KERNEL_SELECT)[1]
+    assert launches == (layers, 0), "expected one kernel per layer and step, got %s" % (launches,)
     pool.profile(0)
     ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
@@ -513,12 +514,11 @@ def main():
 
     # one kernel per step (the step kernel chooses the prompt pages too) or a
     # selection kernel in front?
-    pool.profile((1 << KERNEL_EPILOGUE) | (1 << KERNEL_SELECT))
+    pool.profile(1 << KERNEL_SELECT)
     run(fill + args.warmup, 1)
-    fused = pool.profile_read(KERNEL_EPILOGUE)[1] == 0
     # the event span times the step kernel alone only when it is the step's
     # only launch (a separate prompt selection adds a kernel in front)
-    alone = fused and pool.profile_read(KERNEL_SELECT)[1] == 0
+    alone = pool.profile_read(KERNEL_SELECT)[1] == 0
     pool.profile(0)
     t_start = fill + args.warmup + 1
     st = pool.export_state(0)
@@ -547,7 +547,7 @@ def main():
         run(t_start, args.steps)
     else:
         for i0 in range(0, args.steps, 16):
-            pool.profile((1 << KERNEL_STEP) | (1 << KERNEL_EPILOGUE) | (1 << KERNEL_SELECT))
+            pool.profile((1 << KERNEL_STEP) | (1 << KERNEL_SELECT))
             run(t_start + i0, 1)
             pool.profile(0)
             run(t_start + i0 + 1, min(16, args.steps - i0) - 1)
@@ -556,7 +556,6 @@ def main():
     elapsed = time.perf_counter() - t0
     span_ms = ev0.elapsed_time(ev1)
     step_ms, step_n = pool.profile_read(KERNEL_STEP)
-    epi_ms, epi_n = pool.profile_read(KERNEL_EPILOGUE)
     sel_ms, sel_n = pool.profile_read(KERNEL_SELECT)
     st_end = pool.export_state(0)
     pool.close()
@@ -613,12 +612,11 @@ def main():
             "avg_launch_us": round(step_avg_s * 1e6, 3),
             "launches_timed": args.steps * nl if alone else step_n,
             "timing": "event span over the timed launches" if alone else "per-launch events, every 16th step",
-            "epilogue_kernel_avg_us": round(epi_ms * 1e3 / epi_n, 3) if epi_n else None,
             "select_kernel_avg_us": round(sel_ms * 1e3 / sel_n, 3) if sel_n else None,
         },
     }
     assert np.all(st_end["clock"] == w.prefill_len + t_start + args.steps)
-    if nl == 1 and fused and not variant and not args.no_cold and not args.splits:
+    if nl == 1 and alone and not variant and not args.no_cold and not args.splits:
         line["roofline_cold"] = cold_row(w, args, kernel_b)
     if not args.no_cpu_baseline:
         if scope == raas.SCOPE_KV_HEAD:
