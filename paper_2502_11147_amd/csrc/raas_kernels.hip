@@ -846,6 +846,7 @@ __device__ __forceinline__ void evict_wave(const LayerView& L, const UnitRec& ur
 // lo: where the rank count starts, at most the first slot that a ranked
 // page can occupy (slots below the decode base, and below the unit's pinned
 // pages unless the pool ranks them, hold none).
+template <bool F32>
 __device__ __forceinline__ void retention_wave(const LayerView& L, const UnitRec& ur, double r, const double* s_score,
                                int* s_state, int* s_ts, const int* s_lid, RetShared& out, int lo) {
     const int S = L.S, lane = threadIdx.x & 63, s_lo = lo;
@@ -862,20 +863,23 @@ __device__ __forceinline__ void retention_wave(const LayerView& L, const UnitRec
         // counter, hence two; unrolled by 8 (one counter) 64 slots took as long
         // as one score per read (8 units, 64 slots, us per step: one per read
         // 13.23, two with one counter 13.30, so 13.14; 1 unit, 48 slots 12.18,
-        // 12.01, 11.94; 1 unit, 112 slots 17.56, 16.31, 15.70)
+        // 12.01, 11.94; 1 unit, 112 slots 17.56, 16.31, 15.70). fp32 pools, with
+        // fewer slots to a block, by 8 (1 unit, 16 slots: 9.31 us with one
+        // counter, 9.36 by 4, 9.25 so)
         const double2* sc2 = reinterpret_cast<const double2*>(s_score);
         const double last = (S & 1) ? s_score[S - 1] : INFINITY;
         for (int s0 = s_lo; s0 < S; s0 += 64) {
             const int p = s0 + lane;
             if (p < S && s_state[p] == kEvictable) {
                 const double sp = s_score[p];
-                int less = last < sp ? 1 : 0, less1 = 0;
-#pragma unroll 4
+                int less = !F32 && last < sp ? 1 : 0, less1 = 0;
+#pragma unroll(F32 ? 8 : 4)
                 for (int o = s_lo >> 1; o < S >> 1; ++o) {
                     const double2 x = sc2[o];
                     less += x.x < sp ? 1 : 0;
                     less1 += x.y < sp ? 1 : 0;
                 }
+                if (F32 && (S & 1) && last < sp) ++less;
                 if (less + less1 >= n - k) s_ts[p] = ur.clock;
             }
         }
@@ -1905,7 +1909,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
         // is on the critical path: its count skips the pinned pages; mid-loop
         // it overlaps the streaming, and the narrower count measured no faster)
         if (fused && w == 0)
-            retention_wave(L, ur, r, s_score, s_state, s_ts, s_lid, ret,
+            retention_wave<F32>(L, ur, r, s_score, s_state, s_ts, s_lid, ret,
                            AGG && !L.rank_pinned ? max(L.dbase, pinned) : L.dbase);
         decided = true;
     };
