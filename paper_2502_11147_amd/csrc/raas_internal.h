@@ -89,7 +89,7 @@ struct StepIO {
 
 // Launch plan of one decode step.
 struct StepPlan {
-    int waves;       // wavefronts per step workgroup (bf16)
+    int waves;       // wavefronts per step workgroup
     int nsplit, bps; // splits per unit and blocks per split
     bool fused;      // true: one workgroup per unit, which decides by itself
     bool select_in_step;  // true: the step kernel chooses the prompt pages (no selection kernel)

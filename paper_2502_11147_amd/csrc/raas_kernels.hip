@@ -293,9 +293,10 @@ __global__ __launch_bounds__(kPrefillWaves * 64) void k_prefill(LayerView L, con
 }
 
 // ---------------------------------------------------------------------------
-// Epilogue of a step, for one unit, run by every thread of one workgroup.
-// Slot state is in LDS with the page the step opened already marked
-// evictable; s_score holds the score of every evictable page.
+// The retention rules of a step, for one unit; retention_wave (one workgroup per
+// unit) and retention_block (the last workgroup of a split one) apply them. Slot
+// state is in LDS with the page the step opened already marked evictable;
+// s_score holds the score of every ranked page.
 //  - Top-r refresh (Algorithm 1; Section 3.2): with n evictable pages and
 //    k = floor(r*n), page p gets ts = clock when at least n-k evictable
 //    pages score strictly less, i.e. exactly the pages above the (n-k)-th
@@ -865,7 +866,7 @@ __device__ __forceinline__ void retention_wave(const LayerView& L, const UnitRec
         // 13.23, two with one counter 13.30, so 13.14; 1 unit, 48 slots 12.18,
         // 12.01, 11.94; 1 unit, 112 slots 17.56, 16.31, 15.70). fp32 pools, with
         // fewer slots to a block, by 8 (1 unit, 16 slots: 9.31 us with one
-        // counter, 9.36 by 4, 9.25 so)
+        // counter, 9.36 by 4, 9.29 so)
         const double2* sc2 = reinterpret_cast<const double2*>(s_score);
         const double last = (S & 1) ? s_score[S - 1] : INFINITY;
         for (int s0 = s_lo; s0 < S; s0 += 64) {
@@ -1513,8 +1514,8 @@ __device__ __forceinline__ void attend_block_f32(const u32x4 (&kr)[D / 16], u32x
 // prompt pages itself before its block loop (bounds on the MFMA, exact ones
 // for the pages near the cut), then claims the decode blocks and the chosen
 // prompt blocks from one list. 0: no prompt region.
-// NT: K/V blocks are read with non-temporal loads (pools too large for the
-// memory-side cache to serve the next step).
+// NT: K/V blocks are read with non-temporal loads (too little of the layer is
+// left in the memory-side cache: non_temporal_loads).
 // SPLIT: the unit is spread over several workgroups, or decides with others,
 // and the last workgroup to end finishes the step (instances of their own:
 // in one kernel with the fused ones, that code cost the block loop spills).
@@ -2099,7 +2100,7 @@ __device__ __forceinline__ void step_item(LayerView L, StepIO io, float scale_lo
     }
 }
 
-// Step kernel (bf16 pools): rows a1-a6 for work item blockIdx.x.
+// The step kernel of bf16 pools, work item blockIdx.x.
 template <int D, int NW, bool AGG, int LM, bool NT, bool SPLIT>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_bf16(
     LayerView L, StepIO io, float scale_log2, double r) {
@@ -2597,11 +2598,21 @@ constexpr int kSmallBlocksPerWave = 6;
 constexpr int kFewSlotsBlocksPerWave = 8;
 constexpr int kFewSlots = 64;
 // With a prompt region and fewer units than CUs, fused up to this many
-// attended blocks per wavefront and prompt pages (batch 1 and 8, 128 prompt
-// pages, 72 attended blocks over 8 wavefronts: 30.3 against 36.2 and 32.2
-// against 36.2 us per step; batch 4, 512 pages, 80 blocks: 44.0 against
-// 54.4 us; at 1024 prompt pages the fused workgroup's own bound intervals cost
-// more than the split path's kernels: 68.8 against 45.9 us at batch 1).
+// attended blocks per wavefront and prompt pages. us per step, page 16, the
+// decode blocks and 8 chosen ones, fused / split (intervals, selection, step),
+// cached:
+//     8 units, 128 pages  20.8 / 25.7 at 16 blocks, 25.1 / 26.8 at 40, 31.9 / 27.8 at 72
+//     8 units, 512 pages  30.8 / 29.0, 35.1 / 30.1, 41.5 / 30.9
+//     8 units, 640 pages  41.5 / 30.0, 46.2 / 30.6, 52.8 / 31.7
+//    64 units, 256 pages  24.7 / 30.6, 29.4 / 33.9, 36.5 / 38.4
+//    64 units, 512 pages  31.8 / 32.9, 36.6 / 37.5, 43.7 / 41.6
+//    64 units, 640 pages  43.6 / 35.4, 48.5 / 39.9, 56.0 / 44.3
+//   128 units, 512 pages  32.5 / 39.0, 38.4 / 44.8, 50.5 / 54.6
+// The pages' line lies between 512 and 640 for all of them. The blocks' line was
+// drawn against a split step of two kernels; now that it is one, 8 units would be
+// faster split from about 60 attended blocks on (the static entry point's
+// selection, without the interval kernel, is slower than these figures from 257
+// pages on), and it stands where it was.
 constexpr int kFusedPromptBlocksPerWave = 12;
 constexpr int kFusedPromptPages = 512;
 
