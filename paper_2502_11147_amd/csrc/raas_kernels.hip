@@ -2676,9 +2676,8 @@ StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool b
         // pages itself and attends the chosen blocks and the decode ones,
         // which saves the selection kernel's launch as well
         want = 1;
-    } else if (work <= fused_blocks && (fits || (many_prompt_slots && bf16 && !grouped)) &&
-               (!many_prompt_slots || agg || !bf16)) {
-        want = 1;  // (with many prompt slots also where the fused LDS does not fit)
+    } else if (fits && work <= fused_blocks && (!many_prompt_slots || agg || !bf16)) {
+        want = 1;
     } else {
         want = std::min(std::min(std::max(256 / U, 1), kSplits), (work + 7) / 8);
     }

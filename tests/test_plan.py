@@ -34,7 +34,7 @@ def _plan(U, blocks, G=4, D=128, S=None, bf16=1, agg=0, npr=0, topk=8, cold=0, s
     nprb = npr * page // 32
     work = blocks + min(nprb, topk * max(1, page // 32))
     slots = S if S is not None else (blocks + nprb) * 32 // page
-    lists = 3 + 7 * npr + npr * page // 32 if npr else 0
+    lists = 4 + 6 * npr + npr * page // 32 if npr else 0
     return "plan %d %d %d %d %d %d %d %d %d %d %d %d" % (U, G, D, slots, blocks + nprb, work, bf16, agg, lists, splits,
                                                           npr, cold)
 
@@ -58,6 +58,7 @@ SPLITS = [
     # prompt pages chosen by their own kernel
     (dict(U=32, blocks=32, agg=1, npr=256), True), (dict(U=64, blocks=32, agg=1, npr=256), False),
     (dict(U=8, blocks=32, agg=1, npr=1024), False), (dict(U=64, blocks=40, agg=1, npr=1536, cold=1), False),
+    (dict(U=64, blocks=32, agg=1, npr=1664), True),  # (the slots' bounds no longer fit one workgroup's LDS)
 ]
 
 
