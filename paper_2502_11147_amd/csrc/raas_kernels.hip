@@ -1317,7 +1317,15 @@ __device__ __forceinline__ void finish_units(const LayerView& L, const StepIO& i
         if (rk && !L.agg) s_score[s] = sc;
         count_ranked(rk, &s_aux[256]);
     }
-    for (size_t i = tid; i < nhb; i += nth) s_hb[i] = published(L.score + base * G + i);
+    if (nhb > 0) {
+        // no page below first is ranked, so no bound there is read (64 units, 1664
+        // prompt pages, 40 blocks: 61.2 us with them, 57.7 without)
+        const int row = S * G, skip = first * G, len = row - skip;
+        for (int i = tid; i < nu * len; i += nth) {
+            const int h = nu == 1 ? 0 : i / len, at = h * row + skip + i - h * len;
+            s_hb[at] = published(L.score + base * G + at);
+        }
+    }
     if (merge) merge_stage(L, u0, mf, s_ml, tid, nth);
     __syncthreads();
     if (L.agg) {

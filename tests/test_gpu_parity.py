@@ -536,6 +536,10 @@ FINISH_CASES = [
     dict(budget=8 * 530, splits=2, aggregation=1, prefill_len=8 * 470, n_q_heads=32),  # G 16: 68 KB of bounds
     dict(budget=8 * 40, splits=17, scope=1, aggregation=1),
     dict(budget=8 * 65, splits=3, head_dim=64, n_q_heads=28, n_kv_heads=4),
+    # bounds read from the first slot that can be ranked on: none pinned, most pinned, several units deciding
+    dict(budget=8 * 100, splits=3, aggregation=1, prefill_len=0),
+    dict(budget=8 * 100, splits=3, aggregation=1, prefill_len=8 * 93),
+    dict(budget=8 * 100, splits=3, aggregation=1, scope=1, prefill_len=8 * 71, n_q_heads=12, n_kv_heads=4),
 ]
 
 
