@@ -108,7 +108,7 @@ StepPlan plan_step(int U, int G, int D, int S, int Lcap, int work_blocks, bool b
                    int npr, int nkv, bool cold);
 // Whether a step that reads `own` bytes of its layer, `others` bytes having
 // been streamed since the layer's last step, takes non-temporal loads.
-bool non_temporal_loads(double own, double others, int units);
+bool non_temporal_loads(double own, double others, int units, bool prompt_region);
 // Quest on the prompt pages: the attended fills and the block list of a step.
 hipError_t launch_prompt_select(const LayerView& L, const StepIO& io, hipStream_t stream);
 // Lets the step kernels of a pool's type, head_dim and group size use more than

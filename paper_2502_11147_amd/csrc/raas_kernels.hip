@@ -2634,7 +2634,8 @@ constexpr int kSmallWorkBlocks = 32;
 // Most blocks that one workgroup attends for a unit (the measurements are at
 // kFusedBlocks). long_prompt: a prompt region of more than kFusedPromptPages,
 // whose slots the last workgroup of a split unit would all read again (64
-// units, 1536 pages, 40 blocks: 57.4 us before, 58.7 split, 52.5 fused).
+// units, 40 blocks: 1536 pages 52.5 us fused; 1664 pages, which no longer fit
+// one workgroup's LDS with the softmax aggregation's bounds, 56.5 split).
 int fused_limit(int U, int G, int D, int S, bool bf16, bool long_prompt, bool cold) {
     if (!bf16) return (U < kHalfUnits ? kFusedBlocks : kFusedBlocksHalf) / 2;
     if (U >= kHalfUnits) return kFusedBlocksHalf;

@@ -30,8 +30,13 @@ using namespace raas;
 // 62.6 / 65.3, 68.7 / 70.0 and 74.3 / 74.6, 512 units of 403 and 470 MB 66.3 /
 // 67.2 and 77.5 / 77.8; 192, 384 and 640 units of 403 to 419 MB 63.0 / 61.5,
 // 68.6 / 66.6 and 80.2 / 77.3).
-bool raas::non_temporal_loads(double own, double others, int units) {
-    return others + own * (units % 256 == 0 ? 4.0 / 7.0 : 2.0 / 3.0) > 256e6;
+// With a prompt region the line lies at four fifths: the pages that a step
+// chooses change, and the representative keys, which every step reads with
+// ordinary loads, keep what the blocks leave them (64 units, 1536 pages, 92 MB,
+// three pools in turn 53.6 / 51.6; alone, 1024 units of 369 MB 71.7 / 69.1, 512
+// of 352 MB 64.0 / 62.3, 256 of 336 and 268 MB 63.3 / 64.6 and 52.3 / 54.3).
+bool raas::non_temporal_loads(double own, double others, int units, bool prompt_region) {
+    return others + own * (prompt_region ? 0.8 : units % 256 == 0 ? 4.0 / 7.0 : 2.0 / 3.0) > 256e6;
 }
 
 namespace {
@@ -320,7 +325,7 @@ bool non_temporal(const raas_pool* p, int layer, double own, bool captured) {
     double others = (p->cfg.n_layers - 1.0) * own;
     if (before != 0 && !p->cfg.deterministic && !captured)
         others = (double)(g_streamed[p->device].load(std::memory_order_relaxed) - before);
-    return raas::non_temporal_loads(own, others, p->U);
+    return raas::non_temporal_loads(own, others, p->U, p->npr > 0);
 }
 
 // One decode step of one layer (raas_decode_step_masked); with

@@ -1,6 +1,6 @@
 // Prints the launch plan and the load kind of the configurations on standard
 // input, one a line: "plan U G D S blocks work bf16 agg list_ints splits npr cold"
-// or "loads own others units" (bytes).
+// or "loads own others units prompt" (bytes).
 #include <stdio.h>
 #include <string.h>
 
@@ -16,8 +16,8 @@ int main() {
             const raas::StepPlan p = raas::plan_step(U, G, D, S, blocks * raas::kBlockTokens, work, bf16 != 0, agg, false,
                                                      list, splits, npr, 1, cold != 0);
             printf("%d %d %d %d\n", p.waves, p.nsplit, p.pool_scratch ? 1 : 0, p.fused ? 1 : 0);
-        } else if (sscanf(line, "loads %lf %lf %d", &own, &others, &U) == 3) {
-            printf("%d\n", raas::non_temporal_loads(own, others, U) ? 1 : 0);
+        } else if (sscanf(line, "loads %lf %lf %d %d", &own, &others, &U, &npr) == 4) {
+            printf("%d\n", raas::non_temporal_loads(own, others, U, npr != 0) ? 1 : 0);
         } else {
             fprintf(stderr, "bad line: %s", line);
             return 1;

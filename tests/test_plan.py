@@ -95,4 +95,10 @@ LOADS = [(256, 268e6, 0, 0), (256, 268e6, 268e6, 1), (104, 104e6, 104e6, 0), (10
 
 @pytest.mark.parametrize("units,own,others,nt", LOADS)
 def test_load_kind(ask, units, own, others, nt):
-    assert ask(["loads %r %r %d" % (own, others, units)]) == [(nt,)]
+    assert ask(["loads %r %r %d 0" % (own, others, units)]) == [(nt,)]
+
+
+@pytest.mark.parametrize("units,own,others,nt", [(64, 88e6, 176e6, 0), (64, 92e6, 184e6, 1), (256, 302e6, 0, 0),
+                                                 (512, 352e6, 0, 1)])
+def test_load_kind_with_a_prompt_region(ask, units, own, others, nt):
+    assert ask(["loads %r %r %d 1" % (own, others, units)]) == [(nt,)]
